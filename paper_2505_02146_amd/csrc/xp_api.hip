@@ -41,6 +41,7 @@ void build_tables()
         n += rs_variants(types[s], g_table[s] + n);
         if (types[s] == XP_F32) n += f32_small_variants(g_table[s] + n);
         n += dl_pair_variants(types[s], g_table[s] + n);
+        n += ua_variants(types[s], g_table[s] + n);
         if (n > kMaxVariants) { fprintf(stderr, "xp: variant table overflow (%d)\n", n); abort(); }
         g_count[s] = n;
     }

@@ -1,0 +1,521 @@
+// MFMA kernel for operands of any alignment: bf16 x bf16 -> fp32 and int8 x int8 -> int32 GEMM, strided-batched GEMM and
+// the NHWC convolution (Table 5 of the paper: GEMM, Batch GEMM, Conv2D NHWC) with extents, pitches and channel counts
+// that are no multiple of a 16-byte chunk: odd sequence lengths and feature counts, a first layer's three channels.
+//
+// The direct-to-LDS kernels need 16-byte rows; here the tiles pass through registers, and a 16-byte load may start at any
+// element (the memory system takes dwordx4 loads at any byte address).  What needs care is only where a chunk is not wholly
+// inside its operand:
+//   GEMM   rows (columns) past the edge are clamped to the last one, their results are not stored; a chunk along K past the
+//          end exists in the last K step only, which takes a checked path (element loads, zeros past K).  A chunk along M
+//          or N may run into the next k row, which is memory of the operand in every step but the last.
+//   conv   for a filter row r the taps (s, c) of a pixel are one run of S*Cin consecutive elements of the image, and of the
+//          filter: K is walked as R runs, each padded to whole chunks.  What of a chunk lies outside the image (left or
+//          right) or past the run is an interval of its elements: it is loaded with the rest and masked with zeros.  Only
+//          where the 16 bytes would leave the tensor, at its first and last few pixels, elements are loaded one by one.
+// Structure: 4 waves, 2 x 2; two LDS buffers; the next step's loads fly while a step is multiplied; one barrier a step.
+// Operands along K lie in LDS as 128-byte rows, operands along M or N as they lie in memory and come back through the
+// transposing reads (ds_read_b64_tr_b16 / _b8).  Blocks are computed transposed (16x16x32 bf16, 16x16x64 int8): a lane
+// stores four consecutive columns at once, at any 4-byte aligned address.
+#include "xp_internal.hpp"
+#include "xp_epilogue.hpp"
+
+#include <type_traits>
+
+namespace xp {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
+
+constexpr int NTH = 256;
+constexpr int STEPB = 128;                // bytes of K a step takes of every row (8 chunks)
+
+struct UaParams {
+    const char *A, *B;
+    char *C;
+    int M, N;
+    long long K;                          // elements
+    int run, R, run_c, steps;             // K as R runs of `run` elements = run_c chunks each; steps of 8 chunks
+    unsigned run_magic;                   // ceil(2^32 / run_c); 0: one run, or one chunk a run
+    int full;                             // the first `full` steps need no checks (GEMM)
+    long long lda_b, ldb_b;               // bytes between rows (along K: of the outer index; along M or N: of k)
+    long long a_ext, b_ext;               // bytes of one operand slice, from its first to past its last element
+    long long ldc, c_plane, strideA_b, strideB_b, strideC;
+    float alpha, beta;
+    int tiles_m, tiles_n, group_m;
+    int H, W, Cin, PQ, Q, sh, sw, ph, pw; // convolution
+};
+
+// the run that chunk number c of K belongs to
+__device__ __forceinline__ unsigned run_of(unsigned c, const UaParams &p)
+{
+    return p.run_magic != 0u ? __umulhi(c, p.run_magic) : (p.R > 1 ? c : 0u);
+}
+
+template <bool INT8> struct Kind;
+template <> struct Kind<false> {
+    static constexpr int ESZ = 2;
+    typedef f32x4 acc_t;
+    typedef float out_t;
+    typedef unsigned short elem;
+    static __device__ __forceinline__ acc_t mma(u32x4 a, u32x4 b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+template <> struct Kind<true> {
+    static constexpr int ESZ = 1;
+    typedef i32x4 acc_t;
+    typedef int out_t;
+    typedef unsigned char elem;
+    static __device__ __forceinline__ acc_t mma(u32x4 a, u32x4 b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+    }
+};
+
+__device__ __forceinline__ u32x4 load16(const char *p) { return *(const u32x4_any *)p; }
+
+// elements lo .. hi-1 of the chunk at p, zeros elsewhere; touches nothing else
+template <int ESZ> __device__ __forceinline__ u32x4 load_some(const char *p, int lo, int hi)
+{
+    u32x4 v = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 16 / ESZ; ++i)
+        if (i >= lo && i < hi) {
+            if constexpr (ESZ == 2) v[i >> 1] |= (unsigned)((const unsigned short *)p)[i] << (16 * (i & 1));
+            else v[i >> 2] |= (unsigned)((const unsigned char *)p)[i] << (8 * (i & 3));
+        }
+    return v;
+}
+
+// bit i set: element i of the chunk counts
+template <int ESZ> __device__ __forceinline__ u32x4 keep(u32x4 v, unsigned bits)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        unsigned m;
+        if constexpr (ESZ == 2) {
+            m = ((unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * d, 1) & 0xffffu) | ((unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * d + 1, 1) << 16);
+        } else {
+            const unsigned n = (bits >> (4 * d)) & 15u;
+            m = ((n * 0x00204081u) & 0x01010101u) * 0xffu;
+        }
+        v[d] &= m;
+    }
+    return v;
+}
+
+// One operand's tile: ROWS rows (or columns) x 128 bytes of K.
+//   OC = false: contiguous along K (in a convolution the A operand: pixels x filter window)
+//   OC = true:  contiguous along the outer index
+template <int ESZ, int ROWS, bool OC>
+struct Operand {
+    static constexpr int EPC = 16 / ESZ;
+    static constexpr int CH = ROWS * 8 / NTH;                    // chunks per thread and step
+    static constexpr int CPR = OC ? ROWS * ESZ / 16 : 8;         // chunks per LDS row
+    static constexpr int RSTEP = NTH / CPR;                      // rows between a thread's chunks
+    static constexpr int ROWB = CPR * 16;
+    static constexpr int BYTES = ROWS * STEPB;
+    static constexpr unsigned ALL = (1u << EPC) - 1;
+
+    // chunk swizzle of an LDS row (bank-conflict-free fragment reads; constant over a thread's rows)
+    static __device__ __forceinline__ int swz(int row)
+    {
+        if constexpr (!OC) return row & 6;
+        else if constexpr (ESZ == 2) return ROWB == 256 ? ((row & 3) | ((row >> 3) & 1) << 2) << 1 : (((row >> 1) & 1) | ((row >> 3) & 1) << 1) << 1;
+        else return ROWB == 128 ? ((row >> 1) & 3) | ((row >> 4) & 1) << 2 : ((row >> 2) & 1) | ((row >> 4) & 1) << 1;
+    }
+    static __device__ __forceinline__ int row_of(int t) { return t / CPR; }
+    static __device__ __forceinline__ int col_of(int t) { return t % CPR; }
+
+    unsigned off[CH];                                            // byte offset of the thread's chunks within a step (from `base`)
+    const char *base;                                            // the tile's first row (column)
+    int t, outer0, outer;
+    long long pitch, room;                                       // room: bytes from `base` to the operand's end
+    u32x4 v[CH];
+    unsigned bits[CH];
+
+    __device__ __forceinline__ void init(const char *op, long long ext, long long pitch_b, int o0, int o_ext, int tid)
+    {
+        t = tid; pitch = pitch_b; outer0 = o0; outer = o_ext;
+        const long long first = OC ? (long long)o0 * ESZ : (long long)o0 * pitch_b;
+        base = op + first;
+        room = ext - first;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int row = row_of(t) + i * RSTEP;
+            if constexpr (OC) off[i] = (unsigned)(row * pitch) + (unsigned)(min(EPC * col_of(t), o_ext - 1 - o0) * ESZ);
+            else off[i] = (unsigned)(min(row, o_ext - 1 - o0) * pitch) + 16 * col_of(t);
+        }
+    }
+    // every chunk of the step lies inside the operand
+    __device__ __forceinline__ void load(int step)
+    {
+        const char *at = base + (OC ? (long long)step * (STEPB / ESZ) * pitch : (long long)step * STEPB);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            v[i] = load16(at + off[i]);
+            bits[i] = ALL;
+        }
+    }
+    // K as p.R runs; zeros past a run, nothing read outside the operand
+    __device__ __forceinline__ void load_checked(int step, const UaParams &p)
+    {
+        if constexpr (!OC) {
+            const unsigned c = 8 * step + col_of(t), r = run_of(c, p);
+            const int e0 = EPC * (int)(c - r * p.run_c);
+            const int n = (int)r < p.R ? min(p.run - e0, EPC) : 0;
+            const long long k_at = ((long long)r * p.run + e0) * ESZ;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const long long at = (long long)(off[i] - 16 * col_of(t)) + k_at;
+                bits[i] = (1u << max(n, 0)) - 1;
+                v[i] = u32x4{0u, 0u, 0u, 0u};
+                if (n > 0) v[i] = at + 16 <= room ? load16(base + at) : load_some<ESZ>(base + at, 0, n);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const unsigned kp = step * (STEPB / ESZ) + row_of(t) + i * RSTEP, r = run_of(kp / EPC, p);
+                const int e = (int)(kp - r * p.run_c * EPC);
+                const bool ok = (int)r < p.R && e < p.run;
+                const int col = min(EPC * col_of(t), outer - 1 - outer0);
+                const long long at = ((long long)r * p.run + e) * pitch + col * ESZ;
+                bits[i] = ok ? ALL : 0u;
+                v[i] = u32x4{0u, 0u, 0u, 0u};
+                if (ok) v[i] = at + 16 <= room ? load16(base + at) : load_some<ESZ>(base + at, 0, min(EPC, outer - outer0 - col));
+            }
+        }
+    }
+    __device__ __forceinline__ void store(char *lds) const
+    {
+        char *at = lds + row_of(t) * ROWB + ((col_of(t) ^ swz(row_of(t))) << 4);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            u32x4 x = v[i];
+            if (__builtin_amdgcn_ballot_w64(bits[i] != ALL) != 0) x = keep<ESZ>(x, bits[i]);
+            *(u32x4 *)(at + i * RSTEP * ROWB) = x;
+        }
+    }
+    // MFMA fragment of rows (columns) 16*blk .. +15, k sub-step s of two
+    static __device__ __forceinline__ u32x4 frag(const char *lds, int blk, int s, int lane)
+    {
+        const int a = lane & 15, g = lane >> 4;
+        if constexpr (!OC) {
+            const int row = blk * 16 + a;
+            return *(const u32x4 *)(lds + row * ROWB + (((4 * s + g) ^ swz(row)) << 4));
+        } else if constexpr (ESZ == 2) {
+            const int row = 32 * s + 8 * g + (a >> 2);
+            const char *at = lds + row * ROWB + (((2 * blk + ((a & 3) >> 1)) ^ swz(row)) << 4) + 8 * (a & 1);
+            const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)at);
+            const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(at + 4 * ROWB));
+            return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        } else {
+            const int row = 64 * s + 16 * g + (a >> 1);
+            const char *at = lds + row * ROWB + ((blk ^ swz(row)) << 4) + 8 * (a & 1);
+            const i32x2 lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2 *)at);
+            const i32x2 hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2 *)(at + 8 * ROWB));
+            return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3));
+        }
+    }
+};
+
+// The A operand of a convolution: output pixels x filter window (see the head of the file).
+template <int ROWS>
+struct Window {
+    typedef Operand<2, ROWS, false> Op;
+    static constexpr int CH = Op::CH;
+    const char *image;
+    int t, at0[CH], h0[CH], lo[CH], hi[CH];                      // the window's first element (byte offset), its first image row, columns inside the image
+    u32x4 v[CH];
+    unsigned bits[CH];
+
+    __device__ __forceinline__ void init(const UaParams &p, int m0, int tid)
+    {
+        t = tid;
+        image = p.A;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const unsigned m = (unsigned)min(m0 + Op::row_of(t) + i * Op::RSTEP, p.M - 1);
+            const unsigned n = m / (unsigned)p.PQ, pq = m - n * (unsigned)p.PQ;
+            const unsigned oy = pq / (unsigned)p.Q, ox = pq - oy * (unsigned)p.Q;
+            const int w0 = (int)ox * p.sw - p.pw;
+            h0[i] = (int)oy * p.sh - p.ph;
+            at0[i] = (int)((((long long)n * p.H + h0[i]) * p.W + w0) * p.Cin * 2);
+            lo[i] = max(0, -w0 * p.Cin);
+            hi[i] = min(p.run, (p.W - w0) * p.Cin);
+        }
+    }
+    __device__ __forceinline__ void load(int step, const UaParams &p)
+    {
+        const unsigned c = 8 * step + Op::col_of(t), r = run_of(c, p);
+        const int e0 = 8 * (int)(c - r * p.run_c);
+        const int at_k = (int)(((long long)r * p.W * p.Cin + e0) * 2);
+        bool odd = false;
+        int at[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int a = min(max(lo[i] - e0, 0), 8), b = min(max(hi[i] - e0, 0), 8);
+            const bool inside = (int)r < p.R && (unsigned)(h0[i] + (int)r) < (unsigned)p.H && a < b;
+            bits[i] = inside ? ((1u << b) - 1) & ~((1u << a) - 1) : 0u;
+            at[i] = inside ? at0[i] + at_k : 0;
+            odd |= at[i] < 0 || at[i] + 16 > (int)p.a_ext;
+        }
+        if (__builtin_amdgcn_ballot_w64(odd) == 0) {
+#pragma unroll
+            for (int i = 0; i < CH; ++i) v[i] = load16(image + (unsigned)at[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                v[i] = u32x4{0u, 0u, 0u, 0u};
+                if (bits[i] == 0u) continue;
+                if (at[i] >= 0 && at[i] + 16 <= (int)p.a_ext) v[i] = load16(image + (unsigned)at[i]);
+                else v[i] = load_some<2>(image + (long long)at[i], min(max(lo[i] - e0, 0), 8), min(max(hi[i] - e0, 0), 8));
+            }
+        }
+    }
+    __device__ __forceinline__ void store(char *lds) const
+    {
+        char *to = lds + Op::row_of(t) * Op::ROWB + ((Op::col_of(t) ^ Op::swz(Op::row_of(t))) << 4);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            u32x4 x = v[i];
+            if (__builtin_amdgcn_ballot_w64(bits[i] != Op::ALL) != 0) x = keep<2>(x, bits[i]);
+            *(u32x4 *)(to + i * Op::RSTEP * Op::ROWB) = x;
+        }
+    }
+};
+
+enum { A_K = 0, A_OC = 1, A_CONV = 2 };
+
+template <bool INT8, int AF, bool B_OC, int BM, int BN>
+__global__ __launch_bounds__(NTH, 2) void ua_kernel(UaParams p)
+{
+    using KD = Kind<INT8>;
+    constexpr int ESZ = KD::ESZ;
+    using OpA = Operand<ESZ, BM, AF == A_OC>;
+    using OpB = Operand<ESZ, BN, B_OC>;
+    constexpr int MI = BM / 32, NI = BN / 32;
+    constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+    __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // workgroup -> tile: one XCD owns a run of consecutive tiles, walked in groups of group_m tile rows
+    int bid = blockIdx.x;
+    const int nb = p.tiles_m * p.tiles_n;
+    if ((nb & 7) == 0) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
+    const int gsz = p.group_m * p.tiles_n;
+    const int grp = bid / gsz, first_m = grp * p.group_m;
+    const int gm = min(p.tiles_m - first_m, p.group_m);
+    const int tm = first_m + (bid % gsz) % gm, tn = (bid % gsz) / gm;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const long long batch = blockIdx.y;
+
+    typename std::conditional<AF == A_CONV, Window<BM>, OpA>::type a;
+    OpB b;
+    if constexpr (AF == A_CONV) a.init(p, m0, tid);
+    else a.init(p.A + batch * p.strideA_b, p.a_ext, p.lda_b, m0, p.M, tid);
+    b.init(p.B + batch * p.strideB_b, p.b_ext, p.ldb_b, n0, p.N, tid);
+
+    auto load = [&](int step) {
+        if constexpr (AF == A_CONV) {
+            a.load(step, p);
+            b.load_checked(step, p);
+        } else if (step < p.full) {
+            a.load(step);
+            b.load(step);
+        } else {
+            a.load_checked(step, p);
+            b.load_checked(step, p);
+        }
+    };
+
+    typename KD::acc_t acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = typename KD::acc_t{0, 0, 0, 0};
+
+    load(0);
+    a.store(lds);
+    b.store(lds + OpA::BYTES);
+    __syncthreads();
+    int cur = 0;
+    for (int step = 0; step < p.steps; ++step) {
+        const bool more = step + 1 < p.steps;                    // uniform
+        if (more) load(step + 1);
+        const char *sa = lds + cur, *sb = sa + OpA::BYTES;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            u32x4 af[MI], bf[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) af[i] = OpA::frag(sa, wm * MI + i, s, lane);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bf[j] = OpB::frag(sb, wn * NI + j, s, lane);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = KD::mma(bf[j], af[i], acc[i][j]);
+        }
+        cur = STAGE - cur;
+        if (more) {
+            a.store(lds + cur);                                  // the buffer every wave finished reading before the last barrier
+            b.store(lds + cur + OpA::BYTES);
+        }
+        __syncthreads();
+    }
+
+    // accumulator register v of lane l: row l & 15, column 4 * (l >> 4) + v
+    using OutT = typename KD::out_t;
+    typedef OutT out4_any __attribute__((ext_vector_type(4), aligned(4)));
+    OutT *C = (OutT *)p.C + batch * p.strideC;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int row0 = m0 + (wm * MI + i) * 16, row = row0 + (lane & 15);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int col0 = n0 + (wn * NI + j) * 16, col = col0 + 4 * (lane >> 4);
+            if constexpr (!INT8) {
+                if (p.c_plane) {
+                    store_block16t_planar(acc[i][j], C, p.c_plane, row0, col0, lane, p.M, p.N, p.alpha);
+                    continue;
+                }
+            }
+            if (row >= p.M) continue;
+            OutT *dst = C + (long long)row * p.ldc + col;
+            if constexpr (INT8) {
+                if (col + 4 <= p.N) *(out4_any *)dst = acc[i][j];
+                else
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (col + v < p.N) dst[v] = acc[i][j][v];
+            } else {
+                if (p.beta == 0.0f && col + 4 <= p.N) {
+                    *(out4_any *)dst = p.alpha * acc[i][j];
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (col + v < p.N) {
+                            float x = p.alpha * acc[i][j][v];
+                            if (p.beta != 0.0f) x = __builtin_fmaf(p.beta, dst[v], x);
+                            dst[v] = x;
+                        }
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------ host side
+
+// contiguous along K (1), along the outer index (2) or neither (0).  An outer extent of one is both: along K if it can be.
+int ua_form(int64_t s_outer, int64_t s_k)
+{
+    return s_k == 1 ? 1 : (s_outer == 1 ? 2 : 0);
+}
+
+template <bool INT8>
+bool ua_operand_ok(int64_t s_outer, int64_t s_k, int64_t outer, int64_t K, int tile)
+{
+    const int64_t esz = INT8 ? 1 : 2, epc = 16 / esz, bk = STEPB / esz;
+    if (ua_form(s_outer, s_k) == 1) return (tile - 1) * s_outer * esz + K * esz < 0x7fffffffLL;
+    // a chunk that starts at the last column may run into the next k row, but not past it
+    return ua_form(s_outer, s_k) == 2 && s_k >= epc && outer <= 0x7fffffffLL && bk * s_k * esz + tile * esz < 0x7fffffffLL;
+}
+
+template <bool INT8, int BM, int BN>
+bool ua_can_run(const Problem &q)
+{
+    const int64_t esz = INT8 ? 1 : 2, epc = 16 / esz;
+    if (q.in_type != (INT8 ? XP_I8 : XP_BF16) || q.K <= 0 || q.batch > 65535) return false;
+    if (q.c_plane && (q.beta != 0.0f || INT8)) return false;
+    if (q.M > 0x3fffffffLL || q.N > 0x3fffffffLL || q.K > 0x3fffffffLL) return false;
+    if (((q.M + BM - 1) / BM) * ((q.N + BN - 1) / BN) > 0x7fffffffLL) return false;
+    if (q.conv) {
+        if (INT8) return false;
+        const int64_t run = q.S * q.Cin, in_bytes = (q.M / (q.P * q.Q)) * q.H * q.W * q.Cin * esz;
+        // 32-bit byte offsets, window parts outside the image included; an image of at least one chunk
+        if (in_bytes < 16 || in_bytes + (q.ph + q.R + 1) * (q.W + q.S) * q.Cin * esz + q.pw * q.Cin * esz >= 0x7fffffffLL) return false;
+        if ((q.W + 2 * q.pw) * q.Cin >= 0x3fffffffLL || q.H + 2 * q.ph >= 0x3fffffffLL || q.P * q.Q >= 0x7fffffffLL) return false;
+        if (q.R * ((run + epc - 1) / epc) + 16 >= 65536) return false;             // the division of a chunk number by run_c is exact below 2^16
+    } else {
+        if (!ua_operand_ok<INT8>(q.a_sm, q.a_sk, q.M, q.K, BM)) return false;
+    }
+    return ua_operand_ok<INT8>(q.b_sn, q.b_sk, q.N, q.K, BN);
+}
+
+template <bool INT8, int BM, int BN>
+hipError_t ua_launch(const Problem &q)
+{
+    const int64_t esz = INT8 ? 1 : 2, epc = 16 / esz;
+    UaParams p;
+    p.A = (const char *)q.A; p.B = (const char *)q.B; p.C = (char *)q.C;
+    p.M = (int)q.M; p.N = (int)q.N; p.K = q.K;
+    const int af = q.conv ? A_CONV : (ua_form(q.a_sm, q.a_sk) == 1 ? A_K : A_OC);
+    const bool b_oc = ua_form(q.b_sn, q.b_sk) == 2;
+    p.R = q.conv ? (int)q.R : 1;
+    p.run = q.conv ? (int)(q.S * q.Cin) : (int)q.K;
+    p.run_c = (int)((p.run + epc - 1) / epc);
+    p.run_magic = p.R == 1 || p.run_c == 1 ? 0u : (unsigned)(((1ull << 32) + p.run_c - 1) / p.run_c);
+    p.steps = (int)(((int64_t)p.R * p.run_c + 7) / 8);
+    p.lda_b = (af == A_OC ? q.a_sk : q.a_sm) * esz;
+    p.ldb_b = (b_oc ? q.b_sk : q.b_sn) * esz;
+    p.a_ext = q.conv ? (q.M / (q.P * q.Q)) * q.H * q.W * q.Cin * esz
+                     : ((af == A_OC ? (q.K - 1) * q.a_sk + q.M : (q.M - 1) * q.a_sm + q.K)) * esz;
+    p.b_ext = (b_oc ? (q.K - 1) * q.b_sk + q.N : (q.N - 1) * q.b_sn + q.K) * esz;
+    // unchecked steps: all of K inside, and for an operand along M or N a k row after the step's last one
+    p.full = (int)((q.K - (af == A_OC || b_oc ? 1 : 0)) / (STEPB / esz));
+    p.ldc = q.ldc; p.c_plane = q.c_plane;
+    p.strideA_b = q.strideA * esz; p.strideB_b = q.strideB * esz; p.strideC = q.strideC;
+    p.alpha = q.alpha; p.beta = q.beta;
+    p.tiles_m = (int)((q.M + BM - 1) / BM);
+    p.tiles_n = (int)((q.N + BN - 1) / BN);
+    p.group_m = p.tiles_m < 8 ? p.tiles_m : 8;
+    p.H = (int)q.H; p.W = (int)q.W; p.Cin = (int)q.Cin; p.PQ = (int)(q.P * q.Q); p.Q = (int)q.Q;
+    p.sh = (int)q.sh; p.sw = (int)q.sw; p.ph = (int)q.ph; p.pw = (int)q.pw;
+    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)q.batch);
+#define XP_UA(AF, BO) hipLaunchKernelGGL((ua_kernel<INT8, AF, BO, BM, BN>), grid, dim3(NTH), 0, q.stream, p)
+    if (af == A_K) { if (b_oc) XP_UA(A_K, true); else XP_UA(A_K, false); }
+    else if (af == A_OC) { if (b_oc) XP_UA(A_OC, true); else XP_UA(A_OC, false); }
+    else if constexpr (!INT8) { if (b_oc) XP_UA(A_CONV, true); else XP_UA(A_CONV, false); }
+#undef XP_UA
+    return hipGetLastError();
+}
+
+template <int BM, int BN>
+double ua_cost(const Problem &q)
+{
+    return 1.5 * tile_cost_us(q, BM, BN, 2 * (BM + BN) * STEPB, NTH, 0.45, q.in_type == XP_I8 ? 1 : 2);
+}
+
+#define XP_UA_VARIANT(NAME, TYPE, INT8, BM, BN) \
+    const Variant NAME = {TYPE " " #BM "x" #BN "x128B waves 2x2 any alignment, through registers, mfma16", ua_can_run<INT8, BM, BN>, ua_launch<INT8, BM, BN>, ua_cost<BM, BN>};
+
+XP_UA_VARIANT(kBfUa128, "bf16", false, 128, 128)
+XP_UA_VARIANT(kBfUa128x64, "bf16", false, 128, 64)
+XP_UA_VARIANT(kBfUa64, "bf16", false, 64, 64)
+XP_UA_VARIANT(kI8Ua128, "i8", true, 128, 128)
+XP_UA_VARIANT(kI8Ua128x64, "i8", true, 128, 64)
+XP_UA_VARIANT(kI8Ua64, "i8", true, 64, 64)
+
+}  // namespace
+
+int ua_variants(xp_dtype in_type, const Variant **out)
+{
+    if (in_type == XP_BF16) { out[0] = &kBfUa128; out[1] = &kBfUa128x64; out[2] = &kBfUa64; return 3; }
+    if (in_type == XP_I8) { out[0] = &kI8Ua128; out[1] = &kI8Ua128x64; out[2] = &kI8Ua64; return 3; }
+    return 0;
+}
+
+}  // namespace xp
