@@ -2,35 +2,38 @@
 // the NHWC convolution (Table 5 of the paper: GEMM, Batch GEMM, Conv2D NHWC) with extents, pitches and channel counts
 // that are no multiple of a 16-byte chunk: odd sequence lengths and feature counts, a first layer's three channels.
 //
-// The direct-to-LDS kernels need 16-byte rows; here the tiles pass through registers, and a 16-byte load may start at any
-// element (the memory system takes dwordx4 loads at any byte address).  What needs care is only where a chunk is not wholly
-// inside its operand:
+// The direct-to-LDS kernels need 16-byte rows; here the tiles pass through registers, and a chunk may start at any
+// element (a 16-byte load at an odd multiple of 2 bytes costs 10 to 20 % of the kernel: 2048 x 1024 x 1534 17.0 us, x 1535
+// 17.3 to 18.5; cutting chunks out of dword-aligned loads instead was slower, 30 us against 27 at 2049 x 1021 x 1535, whether
+// the fifth dword was loaded or taken from the next lane).  Care is needed where a chunk is not wholly inside its operand:
 //   GEMM   rows (columns) past the edge are clamped to the last one, their results are not stored; a chunk along K past the
-//          end exists in the last K step only, which takes a checked path (element loads, zeros past K).  A chunk along M
-//          or N may run into the next k row, which is memory of the operand in every step but the last.
+//          end exists in the last K step only, which takes a checked path (zeros past K).  A chunk along M or N may run
+//          into the next k row, which is memory of the operand in every step but the last.
 //   conv   for a filter row r the taps (s, c) of a pixel are one run of S*Cin consecutive elements of the image, and of the
 //          filter: K is walked as R runs, each padded to whole chunks.  What of a chunk lies outside the image (left or
-//          right) or past the run is an interval of its elements: it is loaded with the rest and masked with zeros.  Only
-//          where the 16 bytes would leave the tensor, at its first and last few pixels, elements are loaded one by one.
-// Structure: 4 waves, 2 x 2; two LDS buffers; the next step's loads fly while a step is multiplied; one barrier a step.
+//          right) or past the run is an interval of its elements: it is loaded with the rest and masked with zeros.
+// A chunk that would leave the whole operand is loaded from its last (first) 16 bytes and shifted into place.
+// Structure: 4 waves, 2 x 2; two LDS buffers; one to three steps' loads fly while a step is multiplied; one barrier a step.
 // Operands along K lie in LDS as 128-byte rows, operands along M or N as they lie in memory and come back through the
 // transposing reads (ds_read_b64_tr_b16 / _b8).  Blocks are computed transposed (16x16x32 bf16, 16x16x64 int8): a lane
 // stores four consecutive columns at once, at any 4-byte aligned address.
+//
+// Measured against the general kernel it takes over from: 2049 x 1021 x 1535 278 -> 27 us, 4001 x 4003 x 4005 180 us (710 TFLOP/s),
+// int8 128 x 3196 x 4544 915 -> 19 us, 3x3 convolution 8 x 112 x 112 x 34 -> 44 205 -> 22 us.  Bound: a step's chain of LDS writes,
+// barrier and reads (64x64 .. 128x128 tiles, 0.33 .. 0.85 us a step where MFMAs take 0.06 .. 0.25).
 #include "xp_internal.hpp"
+#include "xp_any_align.hpp"
 #include "xp_epilogue.hpp"
+#include "xp_lds_tr.hpp"
 
+#include <climits>
 #include <type_traits>
 
 namespace xp {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 
@@ -59,64 +62,20 @@ __device__ __forceinline__ unsigned run_of(unsigned c, const UaParams &p)
     return p.run_magic != 0u ? __umulhi(c, p.run_magic) : (p.R > 1 ? c : 0u);
 }
 
-template <bool INT8> struct Kind;
-template <> struct Kind<false> {
-    static constexpr int ESZ = 2;
-    typedef f32x4 acc_t;
-    typedef float out_t;
-    typedef unsigned short elem;
-    static __device__ __forceinline__ acc_t mma(u32x4 a, u32x4 b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    }
-};
-template <> struct Kind<true> {
-    static constexpr int ESZ = 1;
-    typedef i32x4 acc_t;
-    typedef int out_t;
-    typedef unsigned char elem;
-    static __device__ __forceinline__ acc_t mma(u32x4 a, u32x4 b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
-    }
-};
-
-__device__ __forceinline__ u32x4 load16(const char *p) { return *(const u32x4_any *)p; }
-
-// elements lo .. hi-1 of the chunk at p, zeros elsewhere; touches nothing else
-template <int ESZ> __device__ __forceinline__ u32x4 load_some(const char *p, int lo, int hi)
+// all of this wave's LDS reads and writes done, then the workgroup barrier; global loads stay in flight
+__device__ __forceinline__ void wg_barrier()
 {
-    u32x4 v = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int i = 0; i < 16 / ESZ; ++i)
-        if (i >= lo && i < hi) {
-            if constexpr (ESZ == 2) v[i >> 1] |= (unsigned)((const unsigned short *)p)[i] << (16 * (i & 1));
-            else v[i >> 2] |= (unsigned)((const unsigned char *)p)[i] << (8 * (i & 3));
-        }
-    return v;
-}
-
-// bit i set: element i of the chunk counts
-template <int ESZ> __device__ __forceinline__ u32x4 keep(u32x4 v, unsigned bits)
-{
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        unsigned m;
-        if constexpr (ESZ == 2) {
-            m = ((unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * d, 1) & 0xffffu) | ((unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * d + 1, 1) << 16);
-        } else {
-            const unsigned n = (bits >> (4 * d)) & 15u;
-            m = ((n * 0x00204081u) & 0x01010101u) * 0xffu;
-        }
-        v[d] &= m;
-    }
-    return v;
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // One operand's tile: ROWS rows (or columns) x 128 bytes of K.
 //   OC = false: contiguous along K (in a convolution the A operand: pixels x filter window)
 //   OC = true:  contiguous along the outer index
-template <int ESZ, int ROWS, bool OC>
+template <int ESZ, int ROWS, bool OC, int PF>
 struct Operand {
     static constexpr int EPC = 16 / ESZ;
     static constexpr int CH = ROWS * 8 / NTH;                    // chunks per thread and step
@@ -140,8 +99,8 @@ struct Operand {
     const char *base;                                            // the tile's first row (column)
     int t, outer0, outer;
     long long pitch, room;                                       // room: bytes from `base` to the operand's end
-    u32x4 v[CH];
-    unsigned bits[CH];
+    u32x4 v[PF][CH];
+    unsigned bits[PF][CH];
 
     __device__ __forceinline__ void init(const char *op, long long ext, long long pitch_b, int o0, int o_ext, int tid)
     {
@@ -157,17 +116,17 @@ struct Operand {
         }
     }
     // every chunk of the step lies inside the operand
-    __device__ __forceinline__ void load(int step)
+    template <int SET> __device__ __forceinline__ void load(int step)
     {
         const char *at = base + (OC ? (long long)step * (STEPB / ESZ) * pitch : (long long)step * STEPB);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            v[i] = load16(at + off[i]);
-            bits[i] = ALL;
+            v[SET][i] = load16(at + off[i]);
+            bits[SET][i] = ALL;
         }
     }
     // K as p.R runs; zeros past a run, nothing read outside the operand
-    __device__ __forceinline__ void load_checked(int step, const UaParams &p)
+    template <int SET> __device__ __forceinline__ void load_checked(int step, const UaParams &p)
     {
         if constexpr (!OC) {
             const unsigned c = 8 * step + col_of(t), r = run_of(c, p);
@@ -177,9 +136,8 @@ struct Operand {
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
                 const long long at = (long long)(off[i] - 16 * col_of(t)) + k_at;
-                bits[i] = (1u << max(n, 0)) - 1;
-                v[i] = u32x4{0u, 0u, 0u, 0u};
-                if (n > 0) v[i] = at + 16 <= room ? load16(base + at) : load_some<ESZ>(base + at, 0, n);
+                bits[SET][i] = (1u << max(n, 0)) - 1;
+                v[SET][i] = load16_within(base, n > 0 ? at : 0, LLONG_MIN, room);
             }
         } else {
 #pragma unroll
@@ -189,19 +147,18 @@ struct Operand {
                 const bool ok = (int)r < p.R && e < p.run;
                 const int col = min(EPC * col_of(t), outer - 1 - outer0);
                 const long long at = ((long long)r * p.run + e) * pitch + col * ESZ;
-                bits[i] = ok ? ALL : 0u;
-                v[i] = u32x4{0u, 0u, 0u, 0u};
-                if (ok) v[i] = at + 16 <= room ? load16(base + at) : load_some<ESZ>(base + at, 0, min(EPC, outer - outer0 - col));
+                bits[SET][i] = ok ? ALL : 0u;
+                v[SET][i] = load16_within(base, ok ? at : 0, LLONG_MIN, room);
             }
         }
     }
-    __device__ __forceinline__ void store(char *lds) const
+    template <int SET, bool MASK> __device__ __forceinline__ void store(char *lds) const
     {
         char *at = lds + row_of(t) * ROWB + ((col_of(t) ^ swz(row_of(t))) << 4);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            u32x4 x = v[i];
-            if (__builtin_amdgcn_ballot_w64(bits[i] != ALL) != 0) x = keep<ESZ>(x, bits[i]);
+            u32x4 x = v[SET][i];
+            if (MASK && __builtin_amdgcn_ballot_w64(bits[SET][i] != ALL) != 0) x = keep<ESZ>(x, bits[SET][i]);
             *(u32x4 *)(at + i * RSTEP * ROWB) = x;
         }
     }
@@ -229,14 +186,14 @@ struct Operand {
 };
 
 // The A operand of a convolution: output pixels x filter window (see the head of the file).
-template <int ROWS>
+template <int ROWS, int PF>
 struct Window {
-    typedef Operand<2, ROWS, false> Op;
+    typedef Operand<2, ROWS, false, PF> Op;
     static constexpr int CH = Op::CH;
     const char *image;
     int t, at0[CH], h0[CH], lo[CH], hi[CH];                      // the window's first element (byte offset), its first image row, columns inside the image
-    u32x4 v[CH];
-    unsigned bits[CH];
+    u32x4 v[PF][CH];
+    unsigned bits[PF][CH];
 
     __device__ __forceinline__ void init(const UaParams &p, int m0, int tid)
     {
@@ -254,41 +211,26 @@ struct Window {
             hi[i] = min(p.run, (p.W - w0) * p.Cin);
         }
     }
-    __device__ __forceinline__ void load(int step, const UaParams &p)
+    template <int SET> __device__ __forceinline__ void load_checked(int step, const UaParams &p)
     {
         const unsigned c = 8 * step + Op::col_of(t), r = run_of(c, p);
         const int e0 = 8 * (int)(c - r * p.run_c);
         const int at_k = (int)(((long long)r * p.W * p.Cin + e0) * 2);
-        bool odd = false;
-        int at[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int a = min(max(lo[i] - e0, 0), 8), b = min(max(hi[i] - e0, 0), 8);
             const bool inside = (int)r < p.R && (unsigned)(h0[i] + (int)r) < (unsigned)p.H && a < b;
-            bits[i] = inside ? ((1u << b) - 1) & ~((1u << a) - 1) : 0u;
-            at[i] = inside ? at0[i] + at_k : 0;
-            odd |= at[i] < 0 || at[i] + 16 > (int)p.a_ext;
-        }
-        if (__builtin_amdgcn_ballot_w64(odd) == 0) {
-#pragma unroll
-            for (int i = 0; i < CH; ++i) v[i] = load16(image + (unsigned)at[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                v[i] = u32x4{0u, 0u, 0u, 0u};
-                if (bits[i] == 0u) continue;
-                if (at[i] >= 0 && at[i] + 16 <= (int)p.a_ext) v[i] = load16(image + (unsigned)at[i]);
-                else v[i] = load_some<2>(image + (long long)at[i], min(max(lo[i] - e0, 0), 8), min(max(hi[i] - e0, 0), 8));
-            }
+            bits[SET][i] = inside ? ((1u << b) - 1) & ~((1u << a) - 1) : 0u;
+            v[SET][i] = load16_within(image, inside ? at0[i] + at_k : 0, 0, p.a_ext);
         }
     }
-    __device__ __forceinline__ void store(char *lds) const
+    template <int SET, bool MASK> __device__ __forceinline__ void store(char *lds) const
     {
         char *to = lds + Op::row_of(t) * Op::ROWB + ((Op::col_of(t) ^ Op::swz(Op::row_of(t))) << 4);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            u32x4 x = v[i];
-            if (__builtin_amdgcn_ballot_w64(bits[i] != Op::ALL) != 0) x = keep<2>(x, bits[i]);
+            u32x4 x = v[SET][i];
+            if (__builtin_amdgcn_ballot_w64(bits[SET][i] != Op::ALL) != 0) x = keep<2>(x, bits[SET][i]);
             *(u32x4 *)(to + i * Op::RSTEP * Op::ROWB) = x;
         }
     }
@@ -296,13 +238,13 @@ struct Window {
 
 enum { A_K = 0, A_OC = 1, A_CONV = 2 };
 
-template <bool INT8, int AF, bool B_OC, int BM, int BN>
+template <bool INT8, int AF, bool B_OC, int BM, int BN, int PF>
 __global__ __launch_bounds__(NTH, 2) void ua_kernel(UaParams p)
 {
     using KD = Kind<INT8>;
     constexpr int ESZ = KD::ESZ;
-    using OpA = Operand<ESZ, BM, AF == A_OC>;
-    using OpB = Operand<ESZ, BN, B_OC>;
+    using OpA = Operand<ESZ, BM, AF == A_OC, PF>;
+    using OpB = Operand<ESZ, BN, B_OC, PF>;
     constexpr int MI = BM / 32, NI = BN / 32;
     constexpr int STAGE = OpA::BYTES + OpB::BYTES;
     __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE];
@@ -322,22 +264,20 @@ __global__ __launch_bounds__(NTH, 2) void ua_kernel(UaParams p)
     const int m0 = tm * BM, n0 = tn * BN;
     const long long batch = blockIdx.y;
 
-    typename std::conditional<AF == A_CONV, Window<BM>, OpA>::type a;
+    typename std::conditional<AF == A_CONV, Window<BM, PF>, OpA>::type a;
     OpB b;
     if constexpr (AF == A_CONV) a.init(p, m0, tid);
     else a.init(p.A + batch * p.strideA_b, p.a_ext, p.lda_b, m0, p.M, tid);
     b.init(p.B + batch * p.strideB_b, p.b_ext, p.ldb_b, n0, p.N, tid);
 
-    auto load = [&](int step) {
-        if constexpr (AF == A_CONV) {
-            a.load(step, p);
-            b.load_checked(step, p);
-        } else if (step < p.full) {
-            a.load(step);
-            b.load(step);
-        } else {
-            a.load_checked(step, p);
-            b.load_checked(step, p);
+    auto load = [&](int step, auto set_c, auto checked_c) {
+        constexpr int SET = decltype(set_c)::value;
+        if constexpr (decltype(checked_c)::value) {
+            a.template load_checked<SET>(step, p);
+            b.template load_checked<SET>(step, p);
+        } else if constexpr (AF != A_CONV) {
+            a.template load<SET>(step);
+            b.template load<SET>(step);
         }
     };
 
@@ -347,34 +287,74 @@ __global__ __launch_bounds__(NTH, 2) void ua_kernel(UaParams p)
 #pragma unroll
         for (int j = 0; j < NI; ++j) acc[i][j] = typename KD::acc_t{0, 0, 0, 0};
 
-    load(0);
-    a.store(lds);
-    b.store(lds + OpA::BYTES);
-    __syncthreads();
+    // One step of 128 bytes of K, two sub-steps of MFMAs.  Everything else is issued under them: the second sub-step's
+    // fragments are read under the first one's MFMAs, then the next tile goes into the other LDS buffer, and behind the
+    // barrier its first fragments are read under the second sub-step's MFMAs.  PF register sets hold the global loads: step
+    // s + PF is requested during step s.  (Not so woven in a convolution: there more workgroups per compute unit do the
+    // hiding, and the second fragment set's registers cost one; first layer 224 x 224 x 3, 51.7 us against 57.1.)
+    constexpr bool WOVEN = AF != A_CONV;
+    u32x4 af[2][MI], bf[2][NI];
+    auto read = [&](int at, auto s_c) {
+        constexpr int S = decltype(s_c)::value;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) af[S][i] = OpA::frag(lds + at, wm * MI + i, S, lane);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) bf[S][j] = OpB::frag(lds + at + OpA::BYTES, wn * NI + j, S, lane);
+    };
+    auto multiply = [&](auto s_c) {
+        constexpr int S = decltype(s_c)::value;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) acc[i][j] = KD::mma(bf[S][j], af[S][i], acc[i][j]);
+    };
+    constexpr std::integral_constant<int, 0> S0{};
+    constexpr std::integral_constant<int, 1> S1{};
+    static_for<PF>([&](auto u) {
+        if (u < p.steps) {
+            if (AF != A_CONV && u < p.full) load(u, u, std::false_type{});
+            else load(u, u, std::true_type{});
+        }
+    });
+    a.template store<0, true>(lds);
+    b.template store<0, true>(lds + OpA::BYTES);
+    wg_barrier();
+    if constexpr (WOVEN) read(0, S0);
     int cur = 0;
-    for (int step = 0; step < p.steps; ++step) {
-        const bool more = step + 1 < p.steps;                    // uniform
-        if (more) load(step + 1);
-        const char *sa = lds + cur, *sb = sa + OpA::BYTES;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            u32x4 af[MI], bf[NI];
-#pragma unroll
-            for (int i = 0; i < MI; ++i) af[i] = OpA::frag(sa, wm * MI + i, s, lane);
-#pragma unroll
-            for (int j = 0; j < NI; ++j) bf[j] = OpB::frag(sb, wn * NI + j, s, lane);
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j] = KD::mma(bf[j], af[i], acc[i][j]);
+    // u: the register set of the step; CHECK: loads may need checks; LAST: steps may be over (a condition around a load makes
+    // the waits for older ones stricter than they need be, so only the last few steps have it)
+    auto one = [&](int step, auto u_c, auto check_c, auto last_c) {
+        constexpr int U = decltype(u_c)::value, NX = (U + 1) % PF;
+        constexpr bool CHECK = decltype(check_c)::value, LAST = decltype(last_c)::value;
+        if (!LAST || step + PF < p.steps) load(step + PF, u_c, check_c);
+        const bool next = !LAST || step + 1 < p.steps;
+        if constexpr (WOVEN) {
+            read(cur, S1);
+            multiply(S0);
+        } else {
+            read(cur, S0);
+            multiply(S0);
+            read(cur, S1);
+            multiply(S1);
         }
         cur = STAGE - cur;
-        if (more) {
-            a.store(lds + cur);                                  // the buffer every wave finished reading before the last barrier
-            b.store(lds + cur + OpA::BYTES);
+        if (next) {
+            a.template store<NX, CHECK>(lds + cur);               // the buffer every wave finished reading before the last barrier
+            b.template store<NX, CHECK>(lds + cur + OpA::BYTES);
+            wg_barrier();
+            if constexpr (WOVEN) read(cur, S0);
         }
-        __syncthreads();
-    }
+        if constexpr (WOVEN) multiply(S1);
+    };
+    int step = 0;
+    constexpr std::integral_constant<bool, AF == A_CONV> checked{};
+    const int plain = AF == A_CONV ? p.steps : p.full;
+    for (; step + 2 * PF <= plain; step += PF)
+        static_for<PF>([&](auto u) { one(step + u, u, checked, std::false_type{}); });
+    for (; step < p.steps; step += PF)
+        static_for<PF>([&](auto u) {
+            if (step + u < p.steps) one(step + u, u, std::true_type{}, std::true_type{});
+        });
 
     // accumulator register v of lane l: row l & 15, column 4 * (l >> 4) + v
     using OutT = typename KD::out_t;
@@ -429,6 +409,8 @@ template <bool INT8>
 bool ua_operand_ok(int64_t s_outer, int64_t s_k, int64_t outer, int64_t K, int tile)
 {
     const int64_t esz = INT8 ? 1 : 2, epc = 16 / esz, bk = STEPB / esz;
+    const int64_t ext = ua_form(s_outer, s_k) == 1 ? (outer - 1) * s_outer + K : (K - 1) * s_k + outer;
+    if (ext * esz < 16) return false;                            // an operand of at least one chunk
     if (ua_form(s_outer, s_k) == 1) return (tile - 1) * s_outer * esz + K * esz < 0x7fffffffLL;
     // a chunk that starts at the last column may run into the next k row, but not past it
     return ua_form(s_outer, s_k) == 2 && s_k >= epc && outer <= 0x7fffffffLL && bk * s_k * esz + tile * esz < 0x7fffffffLL;
@@ -455,7 +437,7 @@ bool ua_can_run(const Problem &q)
     return ua_operand_ok<INT8>(q.b_sn, q.b_sk, q.N, q.K, BN);
 }
 
-template <bool INT8, int BM, int BN>
+template <bool INT8, int BM, int BN, int PF>
 hipError_t ua_launch(const Problem &q)
 {
     const int64_t esz = INT8 ? 1 : 2, epc = 16 / esz;
@@ -485,7 +467,7 @@ hipError_t ua_launch(const Problem &q)
     p.H = (int)q.H; p.W = (int)q.W; p.Cin = (int)q.Cin; p.PQ = (int)(q.P * q.Q); p.Q = (int)q.Q;
     p.sh = (int)q.sh; p.sw = (int)q.sw; p.ph = (int)q.ph; p.pw = (int)q.pw;
     const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)q.batch);
-#define XP_UA(AF, BO) hipLaunchKernelGGL((ua_kernel<INT8, AF, BO, BM, BN>), grid, dim3(NTH), 0, q.stream, p)
+#define XP_UA(AF, BO) hipLaunchKernelGGL((ua_kernel<INT8, AF, BO, BM, BN, PF>), grid, dim3(NTH), 0, q.stream, p)
     if (af == A_K) { if (b_oc) XP_UA(A_K, true); else XP_UA(A_K, false); }
     else if (af == A_OC) { if (b_oc) XP_UA(A_OC, true); else XP_UA(A_OC, false); }
     else if constexpr (!INT8) { if (b_oc) XP_UA(A_CONV, true); else XP_UA(A_CONV, false); }
@@ -493,21 +475,43 @@ hipError_t ua_launch(const Problem &q)
     return hipGetLastError();
 }
 
+// Calls that the direct-to-LDS kernels decline: rows or channel counts that are no multiple of 16 (convolution: 64) bytes,
+// bases that are not aligned, filters along their output channels.
+bool ua_needed(const Problem &q)
+{
+    const int64_t epc = 16 / elem_size(q.in_type);
+    const bool base = (((uintptr_t)q.A | (uintptr_t)q.B) & 15) != 0;
+    if (q.conv) return base || q.Cin % 32 != 0 || q.b_sk != 1 || q.R * q.S > 32;
+    auto rows = [&](int64_t s_outer, int64_t s_k, int64_t outer, int64_t stride) {
+        return stride % epc != 0 || (s_k == 1 ? (s_outer % epc != 0 || q.K % epc != 0) : (s_k % epc != 0 || outer % epc != 0));
+    };
+    return base || rows(q.a_sm, q.a_sk, q.M, q.strideA) || rows(q.b_sn, q.b_sk, q.N, q.strideB);
+}
+
+// Measured (us per K step and tile on a compute unit, misaligned rows; 2049 x 1021 x 1535, 2048 x 1024 x 1535, 4001 x 4003 x
+// 4005, 501 x 503 x 505): 128x128 0.85 alone on its compute unit and 0.71 beside another, 128x64 0.5, 64x64 0.34.  Up to a
+// few tiles per compute unit it is the fullest one that counts.  Where the operands are aligned the direct-to-LDS kernels
+// are up to twice as fast (2048 x 1024 x 1536: 11 us, this kernel 14), whatever their estimates say.
 template <int BM, int BN>
 double ua_cost(const Problem &q)
 {
-    return 1.5 * tile_cost_us(q, BM, BN, 2 * (BM + BN) * STEPB, NTH, 0.45, q.in_type == XP_I8 ? 1 : 2);
+    const double per_cu = (double)((q.M + BM - 1) / BM) * (double)((q.N + BN - 1) / BN) * (double)q.batch / 256.0;
+    const double full = per_cu <= 3.0 ? __builtin_ceil(per_cu) : per_cu;
+    const double chunk = 16.0 / elem_size(q.in_type);
+    const double steps = __builtin_ceil(q.conv ? (double)q.R * __builtin_ceil((double)(q.S * q.Cin) / chunk) / 8.0 : (double)q.K / (8.0 * chunk));
+    const double us = BM * BN == 128 * 128 ? (full <= 1.0 ? 0.85 : 0.71) : (BM * BN == 128 * 64 ? 0.5 : 0.34);
+    return (4.0 + steps * full * us) * (ua_needed(q) ? 1.0 : 8.0);
 }
 
-#define XP_UA_VARIANT(NAME, TYPE, INT8, BM, BN) \
-    const Variant NAME = {TYPE " " #BM "x" #BN "x128B waves 2x2 any alignment, through registers, mfma16", ua_can_run<INT8, BM, BN>, ua_launch<INT8, BM, BN>, ua_cost<BM, BN>};
+#define XP_UA_VARIANT(NAME, TYPE, INT8, BM, BN, PF) \
+    const Variant NAME = {TYPE " " #BM "x" #BN "x128B waves 2x2 any alignment, through registers, mfma16", ua_can_run<INT8, BM, BN>, ua_launch<INT8, BM, BN, PF>, ua_cost<BM, BN>};
 
-XP_UA_VARIANT(kBfUa128, "bf16", false, 128, 128)
-XP_UA_VARIANT(kBfUa128x64, "bf16", false, 128, 64)
-XP_UA_VARIANT(kBfUa64, "bf16", false, 64, 64)
-XP_UA_VARIANT(kI8Ua128, "i8", true, 128, 128)
-XP_UA_VARIANT(kI8Ua128x64, "i8", true, 128, 64)
-XP_UA_VARIANT(kI8Ua64, "i8", true, 64, 64)
+XP_UA_VARIANT(kBfUa128, "bf16", false, 128, 128, 2)
+XP_UA_VARIANT(kBfUa128x64, "bf16", false, 128, 64, 2)
+XP_UA_VARIANT(kBfUa64, "bf16", false, 64, 64, 3)
+XP_UA_VARIANT(kI8Ua128, "i8", true, 128, 128, 2)
+XP_UA_VARIANT(kI8Ua128x64, "i8", true, 128, 64, 2)
+XP_UA_VARIANT(kI8Ua64, "i8", true, 64, 64, 3)
 
 }  // namespace
 
