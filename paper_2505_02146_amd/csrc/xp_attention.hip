@@ -163,13 +163,11 @@ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0
 // above), S^T sums four k steps instead of two; the V tile is two half-tiles of 64 output columns,
 // O^T has eight column blocks instead of four.
 //
-// NW = waves per workgroup (4 or 8), 16 queries each.  The K and V tiles are shared by all of them, so
-// eight waves halve the LDS a query needs and let twice as many waves live on a SIMD; matrix and vector
-// instructions of different waves do not overlap on this hardware (a SIMD issues one or the other:
-// measured, the times add), so what more waves hide is the waiting -- barriers, LDS and load latency.
-// (eight waves at head size 128: two workgroups per compute unit, i.e. four waves per SIMD, need the kernel within 128 registers)
+// NW = waves per workgroup, 16 queries each; they share the K and V tiles.  Matrix and vector instructions of different waves do
+// not overlap on this hardware (a SIMD issues one or the other: measured, the times add), so what more waves hide is the
+// waiting -- barriers, LDS and load latency.
 template <int D, int HV, int NW>
-__global__ __launch_bounds__(64 * NW, (NW == 8 && HV == 2) ? 4 : 1) void attn_mfma_kernel(AttnParams p)
+__global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(AttnParams p)
 {
     constexpr int NS = D + 1;
     constexpr int KT = K_TILE * HV, VT = V_TILE * HV;   // one step's K and V tiles
@@ -294,24 +292,23 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 && HV == 2) ? 4 : 1) void attn_mf
                 for (int v = 0; v < 4; ++v)
                     if (j0 + kb * 16 + 4 * g + v >= Lk) s[kb][v] = c < 0.0f ? INFINITY : -INFINITY;
         }
-        // largest scaled score of the tile: the extreme raw score times c (c may be negative)
+        // largest scaled score of the lane's 16 keys: the extreme raw score times c (c may be negative)
         float mx = s[0][0];
         if (c >= 0.0f) {
 #pragma unroll
             for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i >> 2][i & 3]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
         } else {
 #pragma unroll
             for (int i = 1; i < 16; ++i) mx = fminf(mx, s[i >> 2][i & 3]);
-            mx = fminf(mx, __shfl_xor(mx, 16));
-            mx = fminf(mx, __shfl_xor(mx, 32));
         }
         // The reference maximum `top` only has to keep exp2() in range, the quotient does not depend
         // on it: it is moved (and the sums rescaled) only when some query of the wave would otherwise
-        // exceed it by more than TAU, which after the first tile is rare.
-        const float cand = mx * c;                       // finite: every tile holds at least one key
+        // exceed it by more than TAU, which after the first tile is rare.  Only then is the query's own maximum
+        // over its four lanes needed, two exchanges through LDS that every step used to wait for.
+        float cand = mx * c;
         if (__builtin_amdgcn_ballot_w64(cand > top + TAU) != 0) {
+            cand = fmaxf(cand, __shfl_xor(cand, 16));
+            cand = fmaxf(cand, __shfl_xor(cand, 32));    // finite: every tile holds at least one key
             const float new_top = fmaxf(top, cand);
             const float shrink = __builtin_amdgcn_exp2f(top - new_top);
             top = new_top;
@@ -382,6 +379,245 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 && HV == 2) ? 4 : 1) void attn_mf
     }
 }
 
+// The same with two blocks of 16 queries per wave, which share every K and V fragment it reads.  With one block the eight-wave
+// kernel reads 256 KB of LDS per key tile and workgroup, 2048 cycles at 128 bytes a cycle, as long as its matrix and vector
+// instructions take (1088 + 1060); with two it reads half of that per query, and what is left is the sum of the two
+// (16 x 4096^2 x 128: 140 -> 122 us = 1120 TFLOP/s, 32 x 2048^2 x 128: 77 -> 68 us, of which the test for the reference maximum
+// without exchanges is 5 %; 32 x 2048^2 x 64: 45 -> 42 us).  The registers (236 at head size 128) leave two waves per SIMD,
+// which is enough to hide what has to wait.  Tried on top and no faster: the second block's exponentials dealt out between
+// the first block's P.V MFMAs (130 us), and, with one block, the next tile's Q.K^T MFMAs between this tile's exponentials (165).
+template <int HV, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_wide_kernel(AttnParams p)
+{
+    constexpr int D = 1, NS = D + 1, QB = 2;
+    constexpr int KT = K_TILE * HV, VT = V_TILE * HV;   // one step's K and V tiles
+    constexpr int BPW = 8 / NW;                          // 8-row blocks of a half-tile that one wave loads
+    constexpr int LPS = 2 * BPW * HV;                    // loads a wave issues per step
+    constexpr int BQW = 16 * QB * NW;                    // queries per workgroup
+    __shared__ __attribute__((aligned(1024))) char lds[NS * (KT + VT)];
+    char *const ks = lds, *const vs = lds + NS * KT;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    unsigned bx, by;
+    xcd_batch_remap(bx, by);                            // the query tiles of one problem share an L2: K, V fetched once
+    const int q0 = bx * BQW;
+    const long long b = by;
+
+    const __amdgpu_buffer_rsrc_t rq = make_rsrc(p.Q + b * p.strideQ + (long long)q0 * p.ldq,
+                                                (unsigned)((long long)(min(p.Lq - q0, BQW) - 1) * p.ldq + KROW * HV));
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.K + b * p.strideK, (unsigned)((long long)(p.Lk - 1) * p.ldk + KROW * HV));
+    const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.V + b * p.strideV, (unsigned)((long long)(p.Lk - 1) * p.ldv + KROW * HV));
+
+    // the wave's queries: B operand of S^T, two k steps per 64 head dimensions
+    // The parameters the key-tile loop uses, as values computed here: a parameter the compiler chose to load again
+    // inside the loop would be a scalar load, which shares its counter with the LDS reads that the loop waits for in
+    // part (s_waitcnt lgkmcnt(n), n > 0, assumes in-order return, which scalar loads do not promise)
+    const int ldk = __builtin_amdgcn_readfirstlane((int)p.ldk), ldv = __builtin_amdgcn_readfirstlane((int)p.ldv);
+    const int Lk = __builtin_amdgcn_readfirstlane(p.Lk);
+    u32x4 qf[QB][2 * HV];
+#pragma unroll
+    for (int b2 = 0; b2 < QB; ++b2)
+#pragma unroll
+        for (int s = 0; s < 2 * HV; ++s)
+            qf[b2][s] = __builtin_amdgcn_raw_buffer_load_b128(rq, (unsigned)(((wave * QB + b2) * 16 + r) * p.ldq) + (32 * s + 8 * g) * 2, 0, 0);
+
+    // K tile: 8 wave-level loads of 8 rows each, two per wave, straight into LDS; lane l lands at
+    // row l/8, position l%8 and fetches the chunk whose swizzled position that is
+    const int krow = lane >> 3;
+    const int kchunk = ((lane & 7) ^ (krow & 6)) << 4;   // rows of a load start at multiples of 8: the swizzle term is the lane's
+    auto issue_k = [&](int j0, int koff) {
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+            for (int i = 0; i < BPW; ++i) {
+                const int blk = wave * BPW + i;
+                const unsigned off = (unsigned)((j0 + blk * 8 + krow) * ldk) + hv * KROW + kchunk;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void *)(ks + koff + hv * K_TILE + blk * 1024), 16, off, 0, 0, 0);
+            }
+    };
+    // V tile: the same, from V
+    auto issue_v = [&](int j0, int voff) {
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+            for (int i = 0; i < BPW; ++i) {
+                const int blk = wave * BPW + i;
+                const unsigned off = (unsigned)((j0 + blk * 8 + krow) * ldv) + hv * KROW + kchunk;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void *)(vs + voff + hv * V_TILE + blk * 1024), 16, off, 0, 0, 0);
+            }
+    };
+    // transposing fragment reads: lane a = l%16 of block g addresses key row 4g + (a >> 2) (+ 32h, + 16 for
+    // the second half of the numbering), the 8 bytes at columns 16x + 4*(a & 3) of its half-tile.
+    // vx[x]: the lane's byte offset within a half-tile for column block x (the swizzle makes it a
+    // different register per x); half-tile, k step and second half are instruction offsets
+    const int va = lane & 15;
+    const int vrow = 4 * g + (va >> 2);
+    const int vchunk = (va & 3) >> 1, vsw = vrow & 6;
+    unsigned vx[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) vx[x] = lds_address(vs) + vrow * KROW + 8 * (va & 1) + (((2 * x + vchunk) ^ vsw) << 4);
+    auto read_v = [&](unsigned at, auto slot_c, auto hv_c, auto h_c) {
+        constexpr int OFF = decltype(slot_c)::value * VT + decltype(hv_c)::value * V_TILE + 32 * decltype(h_c)::value * KROW;
+        FragHalves f;                                    // composed into one fragment only after the wait for it
+        f.lo = lds_read_tr16_b64<OFF>(at);
+        f.hi = lds_read_tr16_b64<OFF + 16 * KROW>(at);
+        return f;
+    };
+
+    const float c = p.scale * LOG2E;                     // scores are kept in units of log2
+    float top[QB];
+    f32x4 total[QB];                                     // running sum of the query's probabilities (4 copies)
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0 x 8
+    f32x4 acc[QB][4 * HV];
+#pragma unroll
+    for (int b2 = 0; b2 < QB; ++b2) {
+        top[b2] = -INFINITY;
+        total[b2] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int x = 0; x < 4 * HV; ++x) acc[b2][x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    const int NT = (Lk + BK - 1) / BK;
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+        issue_k(u * BK, u * KT);
+        issue_v(u * BK, u * VT);
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPS * (D - 1)));   // tile 0 (and the queries) have landed
+    wg_barrier();
+
+    // One key tile.  CUR: the ring slot of the tile, a constant (the loop below walks the ring in whole turns), so
+    // that every LDS offset is an instruction constant; MASK: the tile may reach past the last key (only the last
+    // tile can).  Both used to be decided at run time in every step: about 60 of its 160 vector instructions,
+    // and vector instructions are time the matrix pipe stands still.
+    auto step = [&](int t, auto mask_c, auto cur_c) __attribute__((always_inline)) {
+        constexpr bool MASK = decltype(mask_c)::value;
+        constexpr int cur = decltype(cur_c)::value, prev = cur == 0 ? NS - 1 : cur - 1;
+        const int j0 = t * BK;
+        issue_k(j0 + D * BK, prev * KT);                 // slot read one barrier ago
+        issue_v(j0 + D * BK, prev * VT);
+        // S^T: 4 blocks of 16 keys
+        f32x4 s[QB][4];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+#pragma unroll
+            for (int b2 = 0; b2 < QB; ++b2) s[b2][kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            const int row = kb * 16 + r;
+#pragma unroll
+            for (int h = 0; h < 2 * HV; ++h) {
+                const u32x4 kf = *(const u32x4 *)(ks + cur * KT + (h >> 1) * K_TILE + row * KROW + (((4 * (h & 1) + g) ^ (row & 6)) << 4));
+#pragma unroll
+                for (int b2 = 0; b2 < QB; ++b2) s[b2][kb] = mma(kf, qf[b2][h], s[b2][kb]);
+            }
+        }
+        if constexpr (MASK) {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (j0 + kb * 16 + 4 * g + v >= Lk) {
+#pragma unroll
+                        for (int b2 = 0; b2 < QB; ++b2) s[b2][kb][v] = c < 0.0f ? INFINITY : -INFINITY;
+                    }
+        }
+        // (the lane's own largest score decides whether the reference moves, see above)
+        float cand[QB];
+#pragma unroll
+        for (int b2 = 0; b2 < QB; ++b2) {
+            float mx = s[b2][0][0];
+            if (c >= 0.0f) {
+#pragma unroll
+                for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[b2][i >> 2][i & 3]);
+            } else {
+#pragma unroll
+                for (int i = 1; i < 16; ++i) mx = fminf(mx, s[b2][i >> 2][i & 3]);
+            }
+            cand[b2] = mx * c;
+        }
+        if (__builtin_amdgcn_ballot_w64(cand[0] > top[0] + TAU || cand[1] > top[1] + TAU) != 0) {
+#pragma unroll
+            for (int b2 = 0; b2 < QB; ++b2) {
+                float mx = fmaxf(cand[b2], __shfl_xor(cand[b2], 16));
+                mx = fmaxf(mx, __shfl_xor(mx, 32));      // finite: every tile holds at least one key
+                const float new_top = fmaxf(top[b2], mx);
+                const float shrink = __builtin_amdgcn_exp2f(top[b2] - new_top);
+                top[b2] = new_top;
+                total[b2] *= shrink;
+#pragma unroll
+                for (int x = 0; x < 4 * HV; ++x) acc[b2][x] *= shrink;
+            }
+        }
+        u32x4 pf[QB][2];
+#pragma unroll
+        for (int b2 = 0; b2 < QB; ++b2)
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                pf[b2][kb >> 1][(kb & 1) * 2] = pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(s[b2][kb][0], c, -top[b2])),
+                                                          __builtin_amdgcn_exp2f(__builtin_fmaf(s[b2][kb][1], c, -top[b2])));
+                pf[b2][kb >> 1][(kb & 1) * 2 + 1] = pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(s[b2][kb][2], c, -top[b2])),
+                                                              __builtin_amdgcn_exp2f(__builtin_fmaf(s[b2][kb][3], c, -top[b2])));
+            }
+#pragma unroll
+        for (int b2 = 0; b2 < QB; ++b2)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) total[b2] = mma(ones, pf[b2][h], total[b2]);
+        // The V fragments come by transposing reads issued as assembly (see xp_lds_tr.hpp), group by group
+        // (one column block: 2 k steps, 4 reads), AHEAD groups in front of the MFMAs that use them; the
+        // wait before a group's MFMAs leaves the reads of the younger groups outstanding.
+        {
+            constexpr int NG = 4 * HV, AHEAD = 3;
+            FragHalves vf[NG][2];
+            auto load_group = [&](auto gi_c) {
+                constexpr int GI = decltype(gi_c)::value;
+                const unsigned at = vx[GI % 4];
+                vf[GI][0] = read_v(at, cur_c, std::integral_constant<int, GI / 4>{}, std::integral_constant<int, 0>{});
+                vf[GI][1] = read_v(at, cur_c, std::integral_constant<int, GI / 4>{}, std::integral_constant<int, 1>{});
+            };
+            static_for<(AHEAD < NG ? AHEAD : NG)>([&](auto gi_c) { load_group(gi_c); });
+            static_for<NG>([&](auto gi_c) {
+                constexpr int GI = decltype(gi_c)::value;
+                constexpr int YOUNGER = (NG - 1 - GI < AHEAD - 1 ? NG - 1 - GI : AHEAD - 1);
+                lds_wait<4 * YOUNGER>();
+                frag_tie(vf[GI][0]);
+                frag_tie(vf[GI][1]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int b2 = 0; b2 < QB; ++b2) acc[b2][GI] = mma(frag_value(vf[GI][h]), pf[b2][h], acc[b2][GI]);
+                __builtin_amdgcn_sched_barrier(0);       // or the scheduler collects the MFMAs behind the last wait
+                if constexpr (GI + AHEAD < NG) load_group(std::integral_constant<int, GI + AHEAD>{});
+            });
+        }
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPS * (D - 1)));
+        wg_barrier();
+    };
+    // whole turns of the ring over the tiles that lie inside Lk, then what is left: fewer than NS such tiles and,
+    // if Lk is no multiple of the tile, the ragged last one (NS tiles at most; the slots go on from 0)
+    const int NF = Lk / BK;
+    int t = 0;
+    for (; t + NS <= NF; t += NS)
+        static_for<NS>([&](auto u_c) { step(t + decltype(u_c)::value, std::false_type{}, u_c); });
+    static_for<NS>([&](auto u_c) {
+        constexpr int U = decltype(u_c)::value;
+        if (t + U < NF) step(t + U, std::false_type{}, u_c);
+        else if (t + U < NT) step(t + U, std::true_type{}, u_c);
+    });
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));     // no load may outlive the wave
+
+#pragma unroll
+    for (int b2 = 0; b2 < QB; ++b2) {
+        const float inv = 1.0f / total[b2][0];
+        const int q = q0 + (wave * QB + b2) * 16 + r;
+        if (q < p.Lq) {
+            float *dst = p.O + b * p.strideO + (long long)q * p.ldo + 4 * g;
+#pragma unroll
+            for (int x = 0; x < 4 * HV; ++x) *(f32x4 *)(dst + 16 * x) = acc[b2][x] * inv;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------ host side
 
 AttnParams params_elements(const AttnProblem &q)
@@ -427,6 +663,31 @@ bool mfma_can_run(const AttnProblem &q)
     return true;
 }
 
+// Eight waves (256 queries, one workgroup per compute unit) where the workgroups fill whole rounds of 256 and pad no more
+// queries than four waves (128 queries, two per compute unit) would: 16 x 4096^2 x 128 122 us against 132, but 192 x 512^2 x 128
+// (384 workgroups) 44.7 against 38.8.
+bool wide_rounds(const AttnProblem &q)
+{
+    const int64_t n = q.batch * ((q.Lq + 255) / 256), rounds = (n + 255) / 256;
+    return 2 * ((q.Lq + 255) / 256) == (q.Lq + 127) / 128 && n * 10 >= rounds * 256 * 9;
+}
+
+template <int HV>
+hipError_t wide_launch(const AttnProblem &q)
+{
+    AttnParams p = params_elements(q);
+    p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
+    p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
+    if (wide_rounds(q)) {
+        const dim3 grid((unsigned)((q.Lq + 255) / 256), (unsigned)q.batch);
+        hipLaunchKernelGGL((attn_wide_kernel<HV, 8>), grid, dim3(512), 0, q.stream, p);
+    } else {
+        const dim3 grid((unsigned)((q.Lq + 127) / 128), (unsigned)q.batch);
+        hipLaunchKernelGGL((attn_wide_kernel<HV, 4>), grid, dim3(256), 0, q.stream, p);
+    }
+    return hipGetLastError();
+}
+
 template <int D, int HV, int NW>
 hipError_t mfma_launch(const AttnProblem &q)
 {
@@ -447,19 +708,19 @@ const AttnVariant kMfma128d1 = {"bf16 attention head 128, 64 queries x 64-key st
                                 mfma_launch<1, 2, 4>};
 const AttnVariant kMfma128d2 = {"bf16 attention head 128, 64 queries x 64-key steps, prefetch 2, waves 4x1 mfma16", mfma_can_run<2>,
                                 mfma_launch<2, 2, 4>};
-// Eight waves per workgroup pay when there are enough such workgroups: two per compute unit at head size 64, one at
-// head size 128 (swept under sustained load, TFLOP/s with 8 / 4 waves: head 64 -- 32 x 2048^2 732 / 667, 192 x 512^2
-// 550 / 510, but 96 x 512^2 (384 workgroups of 128 queries) 423 / 460 and 48 x 1024^2 528 / 560; head 128 --
-// 32 x 2048^2 891 / 740, 96 x 512^2 (384) 513 / 479, 8 x 4096^2 (256) 856 / 778)
-bool w8_worthwhile_64(const AttnProblem &q) { return q.batch * ((q.Lq + 127) / 128) >= 512; }
-bool w8_worthwhile_128(const AttnProblem &q) { return q.batch * ((q.Lq + 127) / 128) >= 256; }
-const AttnVariant kMfma64w8 = {"bf16 attention head 64, 128 queries x 64-key steps, prefetch 1, waves 8x1 mfma16", mfma_can_run<1>,
-                               mfma_launch<1, 1, 8>, w8_worthwhile_64};
-const AttnVariant kMfma128w8 = {"bf16 attention head 128, 128 queries x 64-key steps, prefetch 1, waves 8x1 mfma16", mfma_can_run<2>,
-                                mfma_launch<1, 2, 8>, w8_worthwhile_128};
+// Two query blocks per wave pay when there are enough such workgroups, us with 2 / 1 (64-query workgroups):
+// head size 128: 32 x 2048^2 68 / 97, 256 x 128 x 512 18.5 / 22, 192 x 512^2 38.8 / 43.6, 40 x 1100^2 39.3 / 41.1, about even
+// at 96 x 512^2 (24.8 / 24.2) and 300 x 200 x 512 (36.2 / 35.4); one query per problem needs no second block
+// (256 x 1 x 2000: 45 / 39).  Head size 64: 32 x 2048^2 42 / 47, but 192 x 512^2 23.9 / 22.5, so in whole rounds only.
+bool wide_worthwhile_64(const AttnProblem &q) { return q.batch * ((q.Lq + 255) / 256) >= 230 && wide_rounds(q); }
+bool wide_worthwhile_128(const AttnProblem &q) { return q.Lq > 64 && q.batch * ((q.Lq + 127) / 128) >= 256; }
+const AttnVariant kMfma64wide = {"bf16 attention head 64, 128 or 256 queries x 64-key steps, prefetch 1, waves 4x1 or 8x1 of 32 queries, mfma16",
+                                 mfma_can_run<1>, wide_launch<1>, wide_worthwhile_64};
+const AttnVariant kMfma128wide = {"bf16 attention head 128, 128 or 256 queries x 64-key steps, prefetch 1, waves 4x1 or 8x1 of 32 queries, mfma16",
+                                  mfma_can_run<2>, wide_launch<2>, wide_worthwhile_128};
 // swept on the 96 x 512 x 512 x 64 workload: a prefetch distance of 1 is as fast as 2 (the step is bound
 // by its own dependency chain, not by load latency) and leaves more LDS free; 3 is slower
-const AttnVariant *const kBf16Table[] = {&kGeneral, &kMfma64d2, &kMfma64d1, &kMfma128d2, &kMfma128d1, &kMfma64w8, &kMfma128w8};   // the last that can run is the default
+const AttnVariant *const kBf16Table[] = {&kGeneral, &kMfma64d2, &kMfma64d1, &kMfma128d2, &kMfma128d1, &kMfma64wide, &kMfma128wide};   // the last that can run is the default
 
 }  // namespace
 
