@@ -42,6 +42,7 @@ void build_tables()
         if (types[s] == XP_F32) n += f32_small_variants(g_table[s] + n);
         n += dl_pair_variants(types[s], g_table[s] + n);
         n += ua_variants(types[s], g_table[s] + n);
+        n += fr_variants(types[s], g_table[s] + n);
         if (n > kMaxVariants) { fprintf(stderr, "xp: variant table overflow (%d)\n", n); abort(); }
         g_count[s] = n;
     }
@@ -160,9 +161,16 @@ int select_uncached(const Problem &q)
 {
     const int learned = runtime_tuned_variant(q);        // shapes tuned in this process or loaded from a file
     if (learned >= 0) return learned;
+    // few rows against a large matrix: the table has no such shapes, its nearest ones have 256 rows
+    const int n = num_variants(q.in_type);
+    if (few_rows_preferred(q)) {
+        const Variant *few;
+        fr_variants(q.in_type, &few);
+        for (int i = 1; i < n; ++i)
+            if (variant(q.in_type, i) == few) return i;
+    }
     const int tuned = tuned_variant(q);
     if (tuned >= 0) return tuned;
-    const int n = num_variants(q.in_type);
     int best = 0;
     double best_cost = variant(q.in_type, 0)->cost(q);
     for (int i = 1; i < n; ++i) {
