@@ -43,6 +43,7 @@ void build_tables()
         n += dl_pair_variants(types[s], g_table[s] + n);
         n += ua_variants(types[s], g_table[s] + n);
         n += fr_variants(types[s], g_table[s] + n);
+        n += fl_variants(types[s], g_table[s] + n);
         if (n > kMaxVariants) { fprintf(stderr, "xp: variant table overflow (%d)\n", n); abort(); }
         g_count[s] = n;
     }

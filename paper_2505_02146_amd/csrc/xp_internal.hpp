@@ -80,6 +80,7 @@ int dl_pair_variants(xp_dtype in_type, const Variant **out);
 int ua_variants(xp_dtype in_type, const Variant **out);
 int fr_variants(xp_dtype in_type, const Variant **out);
 bool few_rows_preferred(const Problem &q);                // the variant of fr_variants can run the call and is the better choice
+int fl_variants(xp_dtype in_type, const Variant **out);
 int gemv_variants(xp_dtype in_type, const Variant **out);
 
 // Pieces of the dispatcher that the run-time tuner uses (xp_api.hip).
