@@ -388,8 +388,12 @@ constexpr int SK = 256;                                  // k per chunk
 constexpr int ST = 32;                                   // tile edge
 
 // LA, LB: how A and B are brought in. 0: any strides, one element per load. 1: the operand is contiguous along k
-// (row-major A, column-major B), 2: contiguous along its own index (column-major A, row-major B); both with every
-// extent, pitch and pointer that the 16-byte loads touch a multiple of four elements. A k-contiguous operand stays
+// (row-major A, column-major B), 2: contiguous along its own index (column-major A, row-major B).  ANY = false: every
+// extent, pitch and pointer that the 16-byte loads touch is a multiple of four elements.  ANY = true: none need be; a group
+// that sticks out of the operand is loaded from its last 16 bytes and moved into place, one that runs into the next row
+// (or the gap before it) is cut off after the load (256 x 227 x 929 12.4 us, 22 with one-element loads).  Loading the
+// next chunk under this one's MFMAs is no faster (13.5).  A
+// k-contiguous operand stays
 // [index][k] in LDS (pitch 260 floats) and a lane reads four consecutive k of its row with one 16-byte read; the
 // other form is [k][index] (pitch 36). The lanes of the lower half of a wave take k = 8q .. 8q+3, those of the upper
 // half 8q+4 .. 8q+7, for A and B alike, so that the four MFMA steps of a group pair equal k (the order of the sum
@@ -427,6 +431,30 @@ struct F32sOperand {
             *(f32x4v *)&S[L == 1 ? idx * PITCH + kk : kk * PITCH + idx] = r[i];
         }
     }
+    // the same at any alignment; ext: elements from P to the operand's end, 4 at least
+    typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+    static __device__ __forceinline__ void load_any(f32x4v (&r)[E4], const float *P, long long pitch, int i0, int I, int k0, int K, int t,
+                                                    long long ext)
+    {
+#pragma unroll
+        for (int i = 0; i < E4; ++i) {
+            int idx, kk;
+            where(t + 256 * i, idx, kk);
+            const int n = i0 + idx < I && k0 + kk < K ? (L == 1 ? K - (k0 + kk) : I - (i0 + idx)) : 0;   // elements that count
+            const long long off = n <= 0 ? 0 : L == 1 ? (long long)(i0 + idx) * pitch + (k0 + kk) : (long long)(k0 + kk) * pitch + (i0 + idx);
+            const long long from = off + 4 > ext ? ext - 4 : off;
+            const f32x4v v = *(const f32x4a *)(P + from);
+            const int by = (int)(off - from);                                      // 0 .. 3
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float x = v[j];
+                if (j < 3) x = by == 1 ? v[j + 1] : x;
+                if (j < 2) x = by == 2 ? v[j + 2] : x;
+                if (j < 1) x = by == 3 ? v[j + 3] : x;
+                r[i][j] = j < n ? x : 0.0f;
+            }
+        }
+    }
     // the four values k .. k+3 of this lane's row or column
     static __device__ __forceinline__ f32x4v read(const float *S, int idx, int k)
     {
@@ -435,7 +463,7 @@ struct F32sOperand {
     }
 };
 
-template <int LA, int LB>
+template <int LA, int LB, bool ANY>
 __global__ __launch_bounds__(256) void f32s_kernel(FParams p)
 {
     static_assert((LA == 0) == (LB == 0), "both operands by 16-byte loads, or neither");
@@ -461,8 +489,14 @@ __global__ __launch_bounds__(256) void f32s_kernel(FParams p)
     for (int k0 = 0; k0 < p.K; k0 += SK) {
         if constexpr (VEC) {
             typename OA::f32x4v ra[OA::E4], rb[OB::E4];
-            OA::load(ra, A, LA == 1 ? p.a_sm : p.a_sk, m0, p.M, k0, p.K, t);
-            OB::load(rb, B, LB == 1 ? p.b_sn : p.b_sk, n0, p.N, k0, p.K, t);
+            const long long a_pitch = LA == 1 ? p.a_sm : p.a_sk, b_pitch = LB == 1 ? p.b_sn : p.b_sk;
+            if constexpr (ANY) {
+                OA::load_any(ra, A, a_pitch, m0, p.M, k0, p.K, t, LA == 1 ? (p.M - 1) * a_pitch + p.K : (p.K - 1) * a_pitch + p.M);
+                OB::load_any(rb, B, b_pitch, n0, p.N, k0, p.K, t, LB == 1 ? (p.N - 1) * b_pitch + p.K : (p.K - 1) * b_pitch + p.N);
+            } else {
+                OA::load(ra, A, a_pitch, m0, p.M, k0, p.K, t);
+                OB::load(rb, B, b_pitch, n0, p.N, k0, p.K, t);
+            }
             if (k0 > 0) __syncthreads();                 // the chunk before has been multiplied by every wave
             OA::store(As, ra, t);
             OB::store(Bs, rb, t);
@@ -552,6 +586,24 @@ int f32s_form(const Problem &q, bool is_a)
     return 0;
 }
 
+// the same at any alignment: an operand of four elements or more, contiguous one way
+int f32s_form_any(const Problem &q, bool is_a)
+{
+    const long long s_idx = is_a ? q.a_sm : q.b_sn, s_k = is_a ? q.a_sk : q.b_sk, ext = is_a ? q.M : q.N;
+    if (s_k == 1) return (ext - 1) * s_idx + q.K >= 4 ? 1 : 0;
+    if (s_idx == 1) return (q.K - 1) * s_k + ext >= 4 ? 2 : 0;
+    return 0;
+}
+
+template <bool ANY>
+void f32s_launch_vec(int la, int lb, const dim3 &grid, hipStream_t stream, const FParams &p)
+{
+    if (la == 1 && lb == 1) hipLaunchKernelGGL((f32s_kernel<1, 1, ANY>), grid, dim3(256), 0, stream, p);
+    else if (la == 1) hipLaunchKernelGGL((f32s_kernel<1, 2, ANY>), grid, dim3(256), 0, stream, p);
+    else if (lb == 1) hipLaunchKernelGGL((f32s_kernel<2, 1, ANY>), grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((f32s_kernel<2, 2, ANY>), grid, dim3(256), 0, stream, p);
+}
+
 hipError_t f32s_launch(const Problem &q)
 {
     FParams p;
@@ -563,25 +615,26 @@ hipError_t f32s_launch(const Problem &q)
     const int tiles_m = (int)((q.M + ST - 1) / ST);
     p.tiles_n = (int)((q.N + ST - 1) / ST);
     const dim3 grid((unsigned)(tiles_m * p.tiles_n), (unsigned)q.batch);
-    const int la = f32s_form(q, true), lb = f32s_form(q, false);
-    if (la == 1 && lb == 1) hipLaunchKernelGGL((f32s_kernel<1, 1>), grid, dim3(256), 0, q.stream, p);
-    else if (la == 1 && lb == 2) hipLaunchKernelGGL((f32s_kernel<1, 2>), grid, dim3(256), 0, q.stream, p);
-    else if (la == 2 && lb == 1) hipLaunchKernelGGL((f32s_kernel<2, 1>), grid, dim3(256), 0, q.stream, p);
-    else if (la == 2 && lb == 2) hipLaunchKernelGGL((f32s_kernel<2, 2>), grid, dim3(256), 0, q.stream, p);
-    else hipLaunchKernelGGL((f32s_kernel<0, 0>), grid, dim3(256), 0, q.stream, p);
+    const int la = f32s_form(q, true), lb = f32s_form(q, false), la_any = f32s_form_any(q, true), lb_any = f32s_form_any(q, false);
+    if (la && lb) f32s_launch_vec<false>(la, lb, grid, q.stream, p);
+    else if (la_any && lb_any) f32s_launch_vec<true>(la_any, lb_any, grid, q.stream, p);
+    else hipLaunchKernelGGL((f32s_kernel<0, 0, false>), grid, dim3(256), 0, q.stream, p);
     return hipGetLastError();
 }
 
 // Calibrated on the device (calls replayed from a HIP graph). With 16-byte loads: about 2.4 us per launch and 2 us
 // per chunk of 256 k (256^3 4.4 us, 512 x 512 x 1024 11.2 us, 64 x 64 x 4096 33 us, each ahead of the tiled kernels:
 // 8.4, 26.5, 97). One element per load: 3 us and 4.5 us per chunk. With more than one workgroup per compute unit the
-// tiled kernels win (1024^2 x 256: 11.0 against 9.3)
+// pipelined tiled kernels win (1024^2 x 256: 11.0 against 9.3).  Those want aligned operands; the ones left for the others
+// load element by element and lose there too: 61 x 1021 x 130 4.95 us here and 8.9, 333 x 999 x 271 11.4 and 14.7,
+// 1001 x 1003 x 1005 36 (along k; 40 mixed) and 47, 1023 x 500 x 1023 22.8 and 47; even at 700 x 701 x 64, where they stay.
 double f32s_cost(const Problem &q)
 {
     const double tiles = (double)((q.M + ST - 1) / ST) * (double)((q.N + ST - 1) / ST) * (double)q.batch;
-    if (tiles > 256.0 || q.K > 8192) return 1e30;
     const double chunks = (double)((q.K + SK - 1) / SK);
-    return f32s_form(q, true) && f32s_form(q, false) ? 2.4 + 2.0 * chunks : 3.0 + 4.5 * chunks;
+    if (f32s_form(q, true) && f32s_form(q, false)) return tiles > 256.0 || q.K > 8192 ? 1e30 : 2.4 + 2.0 * chunks;
+    if (!f32s_form_any(q, true) || !f32s_form_any(q, false)) return tiles > 256.0 || q.K > 8192 ? 1e30 : 3.0 + 4.5 * chunks;
+    return 2.4 + 2.4 * chunks * (tiles <= 256.0 ? 1.0 : 0.7 * tiles / 256.0);
 }
 
 const Variant kF32_small = {"f32 32x32x256 four waves split k, whole chunk in flight, mfma32x32x2", f32s_can_run, f32s_launch, f32s_cost};
