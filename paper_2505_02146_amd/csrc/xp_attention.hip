@@ -5,7 +5,7 @@
 // are rescaled whenever the maximum grows (the usual streaming form of the softmax, which
 // reaches the same quotient as the two-pass definition).
 //
-// Two kernels:
+// The kernels:
 //   general   one wave per query, fp32 VALU arithmetic, any head size, fp32 or bf16 inputs
 //   mfma      bf16 inputs, head size 64 for Q/K and for V: both contractions on the 16x16x32
 //             matrix-core instruction, laid out so that nothing has to be transposed between them
@@ -618,6 +618,193 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wide_kernel(AttnParams p)
     }
 }
 
+// Few queries against a long key cache (one decoding step): at most 16 queries, one block of the matrix instruction.  Bound: K and V
+// are read once, and what counts is how much of them is on its way.  With the keys walked by the whole workgroup one tile is in
+// flight and every step waits at a barrier; here the workgroup's eight waves share out the keys, each with a K and a V tile of
+// its own in LDS and no barrier before the end: K of the next tile is requested as soon as this tile's scores are there, V as
+// soon as its products are, so that 64 KB or more per compute unit are always on their way.  At the end the waves' sums
+// meet in LDS, scaled to the largest of their maxima.  256 x 1 x 2000 x 128 54 -> 46 us (5.7 TB/s); 16 x 1 x 8192 x 128 119 ->
+// 43 us, where 16 compute units take 98 KB a microsecond each.
+// Layouts and steps are those of the kernels above, with tiles of 64 / HV keys.
+template <int HV, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
+{
+    constexpr int TK = 64 / HV;          // keys per tile
+    constexpr int HALF = TK * KROW, KT = HALF * HV, REGION = 2 * KT;   // 16 KB per wave
+    constexpr int LPT = KT / 1024;                       // loads per K or V tile
+    constexpr int KB = TK / 16, HS = TK / 32;
+    __shared__ __attribute__((aligned(1024))) char lds[NW * REGION];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const long long b = blockIdx.x;
+    char *const ks = lds + wave * REGION, *const vs = ks + KT;
+
+    const __amdgpu_buffer_rsrc_t rq = make_rsrc(p.Q + b * p.strideQ, (unsigned)((long long)(p.Lq - 1) * p.ldq + KROW * HV));
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.K + b * p.strideK, (unsigned)((long long)(p.Lk - 1) * p.ldk + KROW * HV));
+    const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.V + b * p.strideV, (unsigned)((long long)(p.Lk - 1) * p.ldv + KROW * HV));
+    // (as values, see above)
+    const int ldk = __builtin_amdgcn_readfirstlane((int)p.ldk), ldv = __builtin_amdgcn_readfirstlane((int)p.ldv);
+    const int Lk = __builtin_amdgcn_readfirstlane(p.Lk);
+    u32x4 qf[2 * HV];
+#pragma unroll
+    for (int s = 0; s < 2 * HV; ++s)
+        qf[s] = __builtin_amdgcn_raw_buffer_load_b128(rq, r < p.Lq ? (unsigned)(r * p.ldq) + (32 * s + 8 * g) * 2 : OOB, 0, 0);
+
+    // the wave's tiles: a contiguous share
+    const int NT = (Lk + TK - 1) / TK;
+    const int first = (int)((long long)NT * wave / NW), last = (int)((long long)NT * (wave + 1) / NW);
+
+    const int krow = lane >> 3;
+    const int kchunk = ((lane & 7) ^ (krow & 6)) << 4;
+    // a tile past the wave's share lies out of range: no memory is touched, and the waits count the same loads
+    auto issue = [&](const __amdgpu_buffer_rsrc_t &rs, char *to, int ld, int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+            for (int i = 0; i < TK / 8; ++i) {
+                const unsigned off = t < last ? (unsigned)((t * TK + i * 8 + krow) * ld) + hv * KROW + kchunk : OOB;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(to + hv * HALF + i * 1024), 16, off, 0, 0, 0);
+            }
+    };
+    auto landed = [&]() __attribute__((always_inline)) {         // all loads but those of the youngest tile
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(LPT) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int va = lane & 15;
+    const int vrow = 4 * g + (va >> 2);
+    const int vchunk = (va & 3) >> 1, vsw = vrow & 6;
+    unsigned vx[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) vx[x] = lds_address(vs) + vrow * KROW + 8 * (va & 1) + (((2 * x + vchunk) ^ vsw) << 4);
+
+    const float c = p.scale * LOG2E;
+    float top = -INFINITY;
+    f32x4 total = {0.0f, 0.0f, 0.0f, 0.0f};
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0 x 8
+    f32x4 acc[4 * HV];
+#pragma unroll
+    for (int x = 0; x < 4 * HV; ++x) acc[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    issue(rk, ks, ldk, first);
+    issue(rv, vs, ldv, first);
+    for (int t = first; t < last; ++t) {
+        landed();                                        // K of this tile
+        f32x4 s[KB];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            s[kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            const int row = kb * 16 + r;
+#pragma unroll
+            for (int h = 0; h < 2 * HV; ++h) {
+                const u32x4 kf = *(const u32x4 *)(ks + (h >> 1) * HALF + row * KROW + (((4 * (h & 1) + g) ^ (row & 6)) << 4));
+                s[kb] = mma(kf, qf[h], s[kb]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile has been read
+        issue(rk, ks, ldk, t + 1);
+        if ((t + 1) * TK > Lk) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (t * TK + kb * 16 + 4 * g + v >= Lk) s[kb][v] = c < 0.0f ? INFINITY : -INFINITY;
+        }
+        float mx = s[0][0];
+        if (c >= 0.0f) {
+#pragma unroll
+            for (int i = 1; i < 4 * KB; ++i) mx = fmaxf(mx, s[i >> 2][i & 3]);
+        } else {
+#pragma unroll
+            for (int i = 1; i < 4 * KB; ++i) mx = fminf(mx, s[i >> 2][i & 3]);
+        }
+        float cand = mx * c;
+        if (__builtin_amdgcn_ballot_w64(cand > top + TAU) != 0) {
+            cand = fmaxf(cand, __shfl_xor(cand, 16));
+            cand = fmaxf(cand, __shfl_xor(cand, 32));
+            const float new_top = fmaxf(top, cand);
+            const float shrink = top == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(top - new_top);
+            top = new_top;
+            total *= shrink;
+#pragma unroll
+            for (int x = 0; x < 4 * HV; ++x) acc[x] *= shrink;
+        }
+        // a share whose scores are all minus infinity counts for nothing beside the others
+        const float ref = top == -INFINITY ? 0.0f : top;
+        u32x4 pf[HS];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            pf[kb >> 1][(kb & 1) * 2] = pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][0], c, -ref)),
+                                                  __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][1], c, -ref)));
+            pf[kb >> 1][(kb & 1) * 2 + 1] = pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][2], c, -ref)),
+                                                      __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][3], c, -ref)));
+        }
+#pragma unroll
+        for (int h = 0; h < HS; ++h) total = mma(ones, pf[h], total);
+        landed();                                        // V of this tile
+        {
+            // (two column blocks of transposing reads in flight, as above)
+            constexpr int NG = 4 * HV, AHEAD = 2;
+            FragHalves vf[NG][HS];
+            auto load_group = [&](auto gi_c) {
+                constexpr int GI = decltype(gi_c)::value;
+                static_for<HS>([&](auto h_c) {
+                    constexpr int OFF = (GI / 4) * HALF + 32 * decltype(h_c)::value * KROW;
+                    vf[GI][h_c].lo = lds_read_tr16_b64<OFF>(vx[GI % 4]);
+                    vf[GI][h_c].hi = lds_read_tr16_b64<OFF + 16 * KROW>(vx[GI % 4]);
+                });
+            };
+            static_for<AHEAD>([&](auto gi_c) { load_group(gi_c); });
+            static_for<NG>([&](auto gi_c) {
+                constexpr int GI = decltype(gi_c)::value;
+                constexpr int YOUNGER = (NG - 1 - GI < AHEAD - 1 ? NG - 1 - GI : AHEAD - 1);
+                lds_wait<2 * HS * YOUNGER>();
+#pragma unroll
+                for (int h = 0; h < HS; ++h) frag_tie(vf[GI][h]);
+#pragma unroll
+                for (int h = 0; h < HS; ++h) acc[GI] = mma(frag_value(vf[GI][h]), pf[h], acc[GI]);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (GI + AHEAD < NG) load_group(std::integral_constant<int, GI + AHEAD>{});
+            });
+        }
+        issue(rv, vs, ldv, t + 1);                       // the last group's wait has seen all reads of the tile
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));     // no load may outlive the loop: the tiles make room for the sums
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+
+    constexpr int TOPS = 4 * HV * 1024, TOTALS = TOPS + 256;
+    static_assert(TOTALS + 256 <= REGION, "the wave's sums fit its tiles");
+#pragma unroll
+    for (int x = 0; x < 4 * HV; ++x) *(f32x4 *)(ks + x * 1024 + lane * 16) = acc[x];
+    *(float *)(ks + TOPS + lane * 4) = top;
+    *(float *)(ks + TOTALS + lane * 4) = total[0];
+    __syncthreads();
+    if (r < p.Lq) {
+        float f[NW], most = -INFINITY, weight = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            f[w] = *(const float *)(lds + w * REGION + TOPS + lane * 4);
+            most = fmaxf(most, f[w]);
+        }
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            f[w] = __builtin_amdgcn_exp2f(f[w] - most);
+            weight += f[w] * *(const float *)(lds + w * REGION + TOTALS + lane * 4);
+        }
+        const float inv = 1.0f / weight;
+        for (int x = wave; x < 4 * HV; x += NW) {        // column block x
+            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += f[w] * *(const f32x4 *)(lds + w * REGION + x * 1024 + lane * 16);
+            *(f32x4 *)(p.O + b * p.strideO + (long long)r * p.ldo + 16 * x + 4 * g) = sum * inv;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------ host side
 
 AttnParams params_elements(const AttnProblem &q)
@@ -688,12 +875,31 @@ hipError_t wide_launch(const AttnProblem &q)
     return hipGetLastError();
 }
 
+// At most 16 queries: the waves share out the keys, eight of them (128 KB of LDS, one workgroup per compute unit) up to 256
+// problems, four (two workgroups) beyond.  Measured us, here and with 64 queries a workgroup: head size 128, one query
+// 16 x 8192 43 / 119, 64 x 4001 44 / 70, 256 x 2000 46 / 54, 512 x 1000 46 / 51, 40 x 300 6.0 / 7.2; head size 64
+// 16 x 8192 23 / 71, 192 x 2248 20 / 31, 512 x 8000 174 / 187, 512 x 384 9.9 / 10.9, 40 x 64 even.  With eight waves for more
+// than 256 problems the second round stands out (300 x 512 x 64 11.9, four 9.4).  Short head-64 problems that fill the
+// second workgroup of a compute unit by less than three quarters are better off where the hardware packs more of them:
+// 300 x 512 9.4 / 9.2, 384 x 300 7.9 / 7.5.
+template <int HV>
+bool few_queries(const AttnProblem &q)
+{
+    if (q.Lq > 16 || q.Lk < 64) return false;
+    return HV == 2 || q.batch <= 256 || q.batch > 448 || q.Lk > 512;
+}
+
 template <int D, int HV, int NW>
 hipError_t mfma_launch(const AttnProblem &q)
 {
     AttnParams p = params_elements(q);
     p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
     p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
+    if (D == 1 && few_queries<HV>(q)) {
+        if (q.batch <= 256) hipLaunchKernelGGL((attn_few_kernel<HV, 8>), dim3((unsigned)q.batch), dim3(512), 0, q.stream, p);
+        else hipLaunchKernelGGL((attn_few_kernel<HV, 4>), dim3((unsigned)q.batch), dim3(256), 0, q.stream, p);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)((q.Lq + 16 * NW - 1) / (16 * NW)), (unsigned)q.batch);
     hipLaunchKernelGGL((attn_mfma_kernel<D, HV, NW>), grid, dim3(64 * NW), 0, q.stream, p);
     return hipGetLastError();
@@ -712,7 +918,7 @@ const AttnVariant kMfma128d2 = {"bf16 attention head 128, 64 queries x 64-key st
 // head size 128: 32 x 2048^2 68 / 97, 256 x 128 x 512 18.5 / 22, 192 x 512^2 38.8 / 43.6, 40 x 1100^2 39.3 / 41.1, about even
 // at 96 x 512^2 (24.8 / 24.2) and 300 x 200 x 512 (36.2 / 35.4); one query per problem needs no second block
 // (256 x 1 x 2000: 45 / 39).  Head size 64: 32 x 2048^2 42 / 47, but 192 x 512^2 23.9 / 22.5, so in whole rounds only.
-bool wide_worthwhile_64(const AttnProblem &q) { return q.batch * ((q.Lq + 255) / 256) >= 230 && wide_rounds(q); }
+bool wide_worthwhile_64(const AttnProblem &q) { return q.Lq > 16 && q.batch * ((q.Lq + 255) / 256) >= 230 && wide_rounds(q); }
 bool wide_worthwhile_128(const AttnProblem &q) { return q.Lq > 64 && q.batch * ((q.Lq + 127) / 128) >= 256; }
 const AttnVariant kMfma64wide = {"bf16 attention head 64, 128 or 256 queries x 64-key steps, prefetch 1, waves 4x1 or 8x1 of 32 queries, mfma16",
                                  mfma_can_run<1>, wide_launch<1>, wide_worthwhile_64};
