@@ -2,8 +2,8 @@
 // layer over the tokens of one decoding step (Table 5 of the paper: GEMM, GEMV-like cases).  bf16 or int8, any alignment.
 //
 // Bound: W is read once (16 x 8192 x 8192: 134 MB), so what counts is how fast a compute unit takes loads; the tiles of the
-// other kernels are mostly padding here and wait for each K step at a barrier (57 us on that call).  A workgroup owns 8, 16
-// or 32 rows of W and all rows of X; its eight waves share out K, each loading its fragments of W and X straight into
+// other kernels are mostly padding here and wait for each K step at a barrier (57 us on that call).  A workgroup owns 8 to 40
+// rows of W and all rows of X; its eight waves share out K, each loading its fragments of W and X straight into
 // registers, D blocks of 128 bytes ahead, with no barrier before the end.  There the partial sums meet in LDS, in the order
 // of the waves.
 //
@@ -15,6 +15,7 @@
 #include "xp_any_align.hpp"
 #include "xp_lds_tr.hpp"
 
+#include <climits>
 #include <type_traits>
 
 namespace xp {
@@ -41,7 +42,8 @@ __global__ __launch_bounds__(64 * NW) void fr_kernel(FrParams p)
     using KD = Kind<INT8>;
     constexpr int ESZ = KD::ESZ, EPC = 16 / ESZ;
     // blocks in flight, by registers: up to 16 rows of X two workgroups share a compute unit (27.5 -> 25.6 us at 16 x 8192 x 8192)
-    constexpr int ROOM = ((MB <= 2 ? 118 : 190) - 4 * WB * MB) / (4 * (WB + MB)), D = ROOM > 8 ? 8 : ROOM;
+    constexpr int ROOM = ((MB <= 2 ? 118 : WB * MB >= 24 ? 214 : 190) - 4 * WB * MB) / (4 * (WB + MB)), D = ROOM > 8 ? 8 : ROOM;
+    static_assert(D >= 1, "at least one block in flight");
     using OutT = typename KD::out_t;
     typedef typename KD::acc_t acc_t;
     __shared__ OutT red[NW][WB * MB][64];
@@ -167,21 +169,39 @@ hipError_t fr_launch_rows(const FrParams &p, int64_t batch, hipStream_t stream)
         if (stream_w) hipLaunchKernelGGL((fr_kernel<INT8, WB, MB, true>), grid, dim3(64 * NW), 0, stream, p);      \
         else hipLaunchKernelGGL((fr_kernel<INT8, WB, MB, false>), grid, dim3(64 * NW), 0, stream, p);              \
     } while (0)
-    if (p.M <= 8) XP_FR(1);
-    else if (p.M <= 16) XP_FR(2);
+    if constexpr (WB != 3 && WB != 5) {                          // (see fr_w_blocks)
+        if (p.M <= 8) { XP_FR(1); return hipGetLastError(); }
+        if (p.M <= 16) { XP_FR(2); return hipGetLastError(); }
+    }
+    if (p.M <= 24) XP_FR(3);
     else if (p.M <= 32) XP_FR(4);
-    else XP_FR(8);
+    else if (p.M <= 48) XP_FR(6);
+    else if constexpr (WB <= 4) XP_FR(8);
 #undef XP_FR
     return hipGetLastError();
 }
 
-// Blocks of 8 rows of W per workgroup.  The more, the less often X is read, but every compute unit should have a workgroup,
-// and two where they fit (16 rows of X: 32-row workgroups 29.0 us at 16 x 8192 x 8192, 16-row ones 27.4; at 64 rows 38 and 53).
+// Rows of X as the kernel loads them
+int fr_rows(int64_t m) { return m <= 8 ? 8 : m <= 16 ? 16 : m <= 24 ? 24 : m <= 32 ? 32 : m <= 48 ? 48 : 64; }
+
+// Blocks of 8 rows of W per workgroup.  The more, the less often X is read, but every compute unit should have a workgroup, and
+// two where they fit (up to 16 rows of X: 32-row workgroups 29.0 us at 16 x 8192 x 8192, 16-row ones 27.4; 8 x 14336 x 4096 27
+// and 20).  Above 16 rows of X a compute unit holds one workgroup, and a last round of a few costs as much as a whole one: the fullest
+// compute unit's loads of W and X decide (with 32 rows, 42 x 9266 x 11712 would be 290 workgroups; 40 make it 232: 48 us, 80 on
+// the 64-row tile; 20 x 10240 x 5120 32 -> 21, 48 x 5435 x 5000 30 -> 19, 32 x 11008 x 4096 30 -> 25).
 int fr_w_blocks(int64_t n, int64_t m, int64_t batch)
 {
-    const int64_t by32 = (n + 31) / 32 * batch;
-    if (by32 >= 512 || (m > 16 && by32 >= 256)) return 4;
-    return (n + 15) / 16 * batch >= 256 ? 2 : 1;
+    if (m <= 16) {
+        if ((n + 31) / 32 * batch >= 512) return 4;
+        return (n + 15) / 16 * batch >= 256 ? 2 : 1;
+    }
+    int best = 1;
+    int64_t least = LLONG_MAX;
+    for (int wb = 1; wb <= (m > 48 ? 4 : 5); ++wb) {
+        const int64_t loads = ((n + 8 * wb - 1) / (8 * wb) * batch + 255) / 256 * (8 * wb + fr_rows(m));
+        if (loads < least) { least = loads; best = wb; }
+    }
+    return best;
 }
 
 template <bool INT8>
@@ -198,7 +218,9 @@ hipError_t fr_launch(const Problem &q)
     p.strideW_b = (sw ? q.strideA : q.strideB) * esz; p.strideX_b = (sw ? q.strideB : q.strideA) * esz; p.strideC = q.strideC;
     p.alpha = q.alpha; p.beta = q.beta;
     const int wb = fr_w_blocks(p.N, p.M, q.batch);
+    if (wb == 5) return fr_launch_rows<INT8, 5>(p, q.batch, q.stream);
     if (wb == 4) return fr_launch_rows<INT8, 4>(p, q.batch, q.stream);
+    if (wb == 3) return fr_launch_rows<INT8, 3>(p, q.batch, q.stream);
     if (wb == 2) return fr_launch_rows<INT8, 2>(p, q.batch, q.stream);
     return fr_launch_rows<INT8, 1>(p, q.batch, q.stream);
 }
@@ -211,13 +233,13 @@ bool fr_aligned(const Problem &q)
 }
 
 // Microseconds: W from memory at 5 TB/s (8 out of the last-level cache), the fullest compute unit's loads of W and X at 45 KB a
-// microsecond, 18 where rows start off a multiple of 4 bytes (64 x 8192 x 8192 37.7 us, 16 x 8191 x 8193 59 us)
+// microsecond (35 above 48 rows of X in several rounds: 60 x 12000 x 9000 92 us, 78 on the 64-row tile), 18 where rows start off a multiple of 4 bytes (64 x 8192 x 8192 37.7 us, 16 x 8191 x 8193 59 us)
 double fr_cost(const Problem &q)
 {
     const double n = (double)(fr_swapped(q) ? q.M : q.N), m = (double)(fr_swapped(q) ? q.N : q.M), kb = (double)q.K * elem_size(q.in_type);
     const int wb = fr_w_blocks((int64_t)n, (int64_t)m, q.batch);
     const double per_cu = __builtin_ceil(__builtin_ceil(n / (8.0 * wb)) * q.batch / 256.0);
-    const double loads = per_cu * (8.0 * wb + (m <= 8 ? 8 : m <= 16 ? 16 : m <= 32 ? 32 : 64)) * kb / (fr_aligned(q) ? 45e3 : 18e3);
+    const double loads = per_cu * (8.0 * wb + fr_rows((int64_t)m)) * kb / (!fr_aligned(q) ? 18e3 : m > 48.0 && per_cu > 1.0 ? 35e3 : 45e3);
     const double w_us = n * kb * q.batch / (n * kb * q.batch >= 6.7e7 ? 5e6 : 8e6);
     return 4.0 + (loads > w_us ? loads : w_us);
 }

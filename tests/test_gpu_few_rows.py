@@ -73,3 +73,21 @@ def test_few_rows_alpha_beta_batched(xp, oracle):
     xp.xp_force_config(1, "bf16", -1)
     assert np.array_equal(c.cpu().numpy(), 2.0 * ref + 3.0 * C0)
 
+
+
+# 17 to 64 rows of X against as many rows of W as make workgroups of 24, 32 and 40 of them, the last one ragged
+@pytest.mark.parametrize("kind", ["bf16", "i8"])
+@pytest.mark.parametrize("few,many,K", [(24, 6001, 300), (20, 10001, 1100), (33, 6008, 520), (48, 10003, 264), (41, 8180, 1111), (64, 6010, 500)])
+def test_few_rows_splits(xp, oracle, kind, few, many, K):
+    import torch
+    make = (lambda s, t: inputs.int8_uniform(s, 1, t)) if kind == "i8" else (lambda s, t: inputs.to_bf16_bits(inputs.normal(s, 1, t)))
+    (a, lda), (b, ldb) = store(make((few, K), 1), "row"), store(make((K, many), 2), "col")
+    ref = oracle.gemm_i8(few, many, K, a, "row", b, "col") if kind == "i8" else oracle.gemm_float(few, many, K, a, "row", b, "col")
+    c = torch.full((few, many), 7, dtype=torch.int32 if kind == "i8" else torch.float32, device="cuda")
+    xp.xp_force_config(0, kind, _variant(xp, 0, kind, "few rows"))
+    xp.xp_gemm(few, many, K, 1.0, dev(a), "row", lda, dev(b), "col", ldb, 0.0, c, "row", many, a_type=kind, b_type=kind)
+    xp.xp_force_config(0, kind, -1)
+    if kind == "i8":
+        assert np.array_equal(c.cpu().numpy(), ref)
+    else:
+        check_float(c.cpu().numpy(), ref, f"{few}x{many}x{K}")
