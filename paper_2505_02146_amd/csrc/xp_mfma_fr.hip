@@ -253,13 +253,16 @@ const Variant kI8Fr = {"i8 few rows x 8 to 32 rows, eight waves split k, through
 // microsecond (40 where W does not fit the last-level cache, 30 where rows are not aligned) and W at 4.6 TB/s (8).
 // Measured us, here and there: 16 x 8192 x 8192 25 and 57, 16 x 4096 x 4096 7.8 and 18.7, 64 x 4096 x 4096 13.1 and 19.2,
 // 64 x 1024 x 16384 35 and 62; on the other side of the line 64 x 16384 x 2048 25 and 20, 32 x 16384 x 1024 10.7 and 7.8,
-// 64 x 8191 x 8193 89 and 71.  A K of less than a block for every wave and an aligned matrix-vector product stay where they were.
+// 64 x 8191 x 8193 89 and 71.  A K of less than a block for every wave and a
+// matrix-vector product with aligned rows (of any length) stay where they were.
 bool few_rows_preferred(const Problem &q)
 {
     if (q.in_type == XP_F32 || !(q.in_type == XP_BF16 ? fr_can_run<false>(q) : fr_can_run<true>(q))) return false;
     const double n = (double)(fr_swapped(q) ? q.M : q.N), kb = (double)q.K * elem_size(q.in_type);
     const bool aligned = fr_aligned(q);
-    if (kb < NW * BLOCKB || (aligned && q.N == 1)) return false;
+    const int64_t epc = 16 / elem_size(q.in_type);
+    const bool gemv = q.N == 1 && (((uintptr_t)q.A | (uintptr_t)q.B) & 15) == 0 && q.a_sm % epc == 0 && q.strideA % epc == 0 && q.strideB % epc == 0;
+    if (kb < NW * BLOCKB || gemv) return false;
     const bool cold = n * kb * q.batch >= 6.7e7;
     const double loads = __builtin_ceil(__builtin_ceil(n / 64.0) * q.batch / 256.0) * 128.0 * kb / (!aligned ? 30e3 : cold ? 40e3 : 70e3);
     const double w_us = n * kb * q.batch / (cold ? 4.6e6 : 8e6);
