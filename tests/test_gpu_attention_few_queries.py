@@ -41,3 +41,25 @@ def test_shares_that_count_for_nothing(xp, d, low):  # noqa: F811
                     q_type="bf16", k_type="bf16", v_type="bf16")
     # rounding the probabilities to bf16 moves each by 2^-9 at most, and the sum of them alike
     assert (o.cpu().double() - ref).norm() <= 2.0 ** -8 * ref.norm()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [0.125, -0.2])
+@pytest.mark.parametrize("Lq", [1, 16])
+def test_a_query_gets_the_same_result_among_few_and_among_many(xp, d, scale, Lq):  # noqa: F811
+    """17 queries take the kernel that walks all keys with one reference maximum.  Rounded to bf16 against the same
+    reference, the probabilities are the same ones; what differs is the order of fp32 sums over 1500 keys, 2^-24 sqrt(1500)
+    = 2.3e-6 of the result and as much for the quotient's sum, taken four times (against other references: 2e-3)."""
+    import torch
+    batch, Lk = 3, 1500
+    Q, K, V = (inputs.to_bf16_bits(inputs.normal((batch, L, d), 7, t)) for L, t in ((17, 1), (Lk, 2), (Lk, 3)))
+    q, k, v = (dev(x.reshape(-1)) for x in (Q, K, V))
+    xp.xp_force_config(xp.XP_OP_ATTENTION, "bf16", -1)
+
+    def call(n):
+        o = torch.full((batch, n, d), float("nan"), device="cuda")
+        xp.xp_attention(batch, n, Lk, d, d, scale * d ** -0.5 * 8, q, d, 17 * d, k, d, Lk * d, v, d, Lk * d, o, d, n * d,
+                        q_type="bf16", k_type="bf16", v_type="bf16")
+        return o.double()
+    few, many = call(Lq), call(17)[:, :Lq]
+    assert (few - many).norm() <= 2e-5 * many.norm()
