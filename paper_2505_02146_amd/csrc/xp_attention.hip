@@ -910,18 +910,20 @@ hipError_t wide_launch(const AttnProblem &q)
     return hipGetLastError();
 }
 
-// At most 16 queries: the waves share out the keys, eight of them (128 KB of LDS, one workgroup per compute unit) up to 256
-// problems, four (two workgroups) beyond.  Measured us, here and with 64 queries a workgroup: head size 128, one query
-// 16 x 8192 43 / 119, 64 x 4001 44 / 70, 256 x 2000 46 / 54, 512 x 1000 46 / 51, 40 x 300 6.0 / 7.2; head size 64
-// 16 x 8192 23 / 71, 192 x 2248 20 / 31, 512 x 8000 174 / 187, 512 x 384 9.9 / 10.9, 40 x 64 even.  With eight waves for more
-// than 256 problems the second round stands out (300 x 512 x 64 11.9, four 9.4).  Short head-64 problems that fill the
-// second workgroup of a compute unit by less than three quarters are better off where the hardware packs more of them:
-// 300 x 512 9.4 / 9.2, 384 x 300 7.9 / 7.5.
+// At most 16 queries: the waves share out the keys, eight of them (129 KB of LDS, one workgroup per compute unit) up to 256
+// problems.  Measured us with K and V from memory, here and with the 64-query workgroups: head size 128, 16 x 8192 72 / 126,
+// 64 x 1000 14.8 / 20.9, 128 x 256 7.7 / 8.0, 256 x 2000 46 / 50.5; head size 64, 16 x 8192 39 / 100, 64 x 1000 9.2 / 14.4,
+// 256 x 512 9.2 / 10.6.  With fewer keys the meeting of the waves costs more than the sharing saves (head size 128,
+// 128 x 192 6.3 / 6.0, 64 x 128 5.6 / 5.0; head size 64, 64 x 256 5.3 / 4.8, x 320 even).  Beyond 256 problems the second
+// round stands out, and 64-query workgroups, of which a compute unit holds more, are as fast or faster (head size 128,
+// 257 x 1000 32.9 / 28.9; head size 64, 300 x 1000 19.4 / 18.1, 512 x 1000 26.8 / 24.6) -- but for 448 problems of head
+// size 128 and more, where four waves share out the keys (two workgroups per compute unit: 512 x 512 25.5 / 27.7,
+// 1024 x 256 25.3 / 32, 448 x 1000 even).
 template <int HV>
 bool few_queries(const AttnProblem &q)
 {
-    if (q.Lq > 16 || q.Lk < 64) return false;
-    return HV == 2 || q.batch <= 256 || q.batch > 448 || q.Lk > 512;
+    if (q.Lq > 16 || q.Lk < (HV == 2 ? 256 : 320)) return false;
+    return q.batch <= 256 || (HV == 2 && q.batch >= 448);
 }
 
 template <int D, int HV, int NW>
@@ -931,8 +933,13 @@ hipError_t mfma_launch(const AttnProblem &q)
     p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
     p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
     if (D == 1 && few_queries<HV>(q)) {
-        if (q.batch <= 256) hipLaunchKernelGGL((attn_few_kernel<HV, 8>), dim3((unsigned)q.batch), dim3(512), 0, q.stream, p);
-        else hipLaunchKernelGGL((attn_few_kernel<HV, 4>), dim3((unsigned)q.batch), dim3(256), 0, q.stream, p);
+        if constexpr (HV == 2) {
+            if (q.batch > 256) {
+                hipLaunchKernelGGL((attn_few_kernel<HV, 4>), dim3((unsigned)q.batch), dim3(256), 0, q.stream, p);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((attn_few_kernel<HV, 8>), dim3((unsigned)q.batch), dim3(512), 0, q.stream, p);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)((q.Lq + 16 * NW - 1) / (16 * NW)), (unsigned)q.batch);

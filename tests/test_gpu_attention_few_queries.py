@@ -8,9 +8,10 @@ from tests.test_gpu_attention import TIGHT, _gate, _run, xp  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-# (batch, Lq, Lk): one tile for eight waves, one and several tiles a wave, a ragged last tile (of one key), all 16 queries,
-# more than 256 problems (four waves)
-CASES = [(1, 1, 64), (2, 16, 65), (3, 1, 512), (2, 8, 513), (2, 15, 1000), (1, 3, 2049), (257, 1, 600), (450, 2, 97)]
+# (batch, Lq, Lk): fewer keys than the waves share out; from 256 (head size 128) and 320 (64) on waves without a tile, one and
+# several tiles a wave, a ragged last tile (of one key), all 16 queries; 256 problems and more, 448 (four waves) and more
+CASES = [(1, 1, 64), (2, 16, 65), (3, 2, 256), (2, 1, 257), (2, 5, 319), (1, 16, 320), (2, 2, 321), (3, 1, 512), (2, 8, 513), (2, 15, 1000),
+         (1, 3, 2049), (256, 1, 400), (257, 1, 600), (447, 1, 300), (448, 1, 257), (450, 2, 97), (450, 3, 520)]
 
 
 @pytest.mark.parametrize("d,variant", [(64, 2), (128, 4)])
