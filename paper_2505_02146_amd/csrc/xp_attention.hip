@@ -163,11 +163,13 @@ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0
 // above), S^T sums four k steps instead of two; the V tile is two half-tiles of 64 output columns,
 // O^T has eight column blocks instead of four.
 //
-// NW = waves per workgroup, 16 queries each; they share the K and V tiles.  Matrix and vector instructions of different waves do
-// not overlap on this hardware (a SIMD issues one or the other: measured, the times add), so what more waves hide is the
-// waiting -- barriers, LDS and load latency.
+// NW = waves per workgroup (4 or 8), 16 queries each.  The K and V tiles are shared by all of them, so
+// eight waves halve the LDS a query needs and let twice as many waves live on a SIMD; matrix and vector
+// instructions of different waves do not overlap on this hardware (a SIMD issues one or the other:
+// measured, the times add), so what more waves hide is the waiting -- barriers, LDS and load latency.
+// (eight waves at head size 128: two workgroups per compute unit, i.e. four waves per SIMD, need the kernel within 128 registers)
 template <int D, int HV, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(AttnParams p)
+__global__ __launch_bounds__(64 * NW, (NW == 8 && HV == 2) ? 4 : 1) void attn_mfma_kernel(AttnParams p)
 {
     constexpr int NS = D + 1;
     constexpr int KT = K_TILE * HV, VT = V_TILE * HV;   // one step's K and V tiles
@@ -379,17 +381,16 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(AttnParams p)
     }
 }
 
-// The same with two blocks of 16 queries per wave, which share every K and V fragment it reads.  With one block the eight-wave
+// Head size 128 with two blocks of 16 queries per wave, which share every K and V fragment it reads.  With one block the eight-wave
 // kernel reads 256 KB of LDS per key tile and workgroup, 2048 cycles at 128 bytes a cycle, as long as its matrix and vector
 // instructions take (1088 + 1060); with two it reads half of that per query, and what is left is the sum of the two
-// (16 x 4096^2 x 128: 140 -> 122 us = 1120 TFLOP/s, 32 x 2048^2 x 128: 77 -> 68 us, of which the test for the reference maximum
-// without exchanges is 5 %; 32 x 2048^2 x 64: 45 -> 42 us).  The registers (236 at head size 128) leave two waves per SIMD,
-// which is enough to hide what has to wait.  Tried on top and no faster: the second block's exponentials dealt out between
+// (16 x 4096^2: 130 -> 122 us = 1120 TFLOP/s, 32 x 2048^2 70 -> 66).  The registers (236) leave two waves per SIMD,
+// which is enough to hide what has to wait, but one workgroup per compute unit, whose start and end nothing hides: the keys
+// have to be many.  Tried on top and no faster: the second block's exponentials dealt out between
 // the first block's P.V MFMAs (130 us), and, with one block, the next tile's Q.K^T MFMAs between this tile's exponentials (165).
-template <int HV, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_wide_kernel(AttnParams p)
+__global__ __launch_bounds__(512, 2) void attn_wide_kernel(AttnParams p)
 {
-    constexpr int D = 1, NS = D + 1, QB = 2;
+    constexpr int HV = 2, NW = 8, D = 1, NS = D + 1, QB = 2;
     constexpr int KT = K_TILE * HV, VT = V_TILE * HV;   // one step's K and V tiles
     constexpr int BPW = 8 / NW;                          // 8-row blocks of a half-tile that one wave loads
     constexpr int LPS = 2 * BPW * HV;                    // loads a wave issues per step
@@ -885,31 +886,6 @@ bool mfma_can_run(const AttnProblem &q)
     return true;
 }
 
-// Eight waves (256 queries, one workgroup per compute unit) where the workgroups fill whole rounds of 256 and pad no more
-// queries than four waves (128 queries, two per compute unit) would: 16 x 4096^2 x 128 122 us against 132, but 192 x 512^2 x 128
-// (384 workgroups) 44.7 against 38.8.
-bool wide_rounds(const AttnProblem &q)
-{
-    const int64_t n = q.batch * ((q.Lq + 255) / 256), rounds = (n + 255) / 256;
-    return 2 * ((q.Lq + 255) / 256) == (q.Lq + 127) / 128 && n * 10 >= rounds * 256 * 9;
-}
-
-template <int HV>
-hipError_t wide_launch(const AttnProblem &q)
-{
-    AttnParams p = params_elements(q);
-    p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
-    p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
-    if (wide_rounds(q)) {
-        const dim3 grid((unsigned)((q.Lq + 255) / 256), (unsigned)q.batch);
-        hipLaunchKernelGGL((attn_wide_kernel<HV, 8>), grid, dim3(512), 0, q.stream, p);
-    } else {
-        const dim3 grid((unsigned)((q.Lq + 127) / 128), (unsigned)q.batch);
-        hipLaunchKernelGGL((attn_wide_kernel<HV, 4>), grid, dim3(256), 0, q.stream, p);
-    }
-    return hipGetLastError();
-}
-
 // At most 16 queries: the waves share out the keys, eight of them (129 KB of LDS, one workgroup per compute unit) up to 256
 // problems.  Measured us with K and V from memory, here and with the 64-query workgroups: head size 128, 16 x 8192 72 / 126,
 // 64 x 1000 14.8 / 20.9, 128 x 256 7.7 / 8.0, 256 x 2000 46 / 50.5; head size 64, 16 x 8192 39 / 100, 64 x 1000 9.2 / 14.4,
@@ -932,7 +908,7 @@ hipError_t mfma_launch(const AttnProblem &q)
     AttnParams p = params_elements(q);
     p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
     p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
-    if (D == 1 && few_queries<HV>(q)) {
+    if (D == 1 && NW == 4 && few_queries<HV>(q)) {
         if constexpr (HV == 2) {
             if (q.batch > 256) {
                 hipLaunchKernelGGL((attn_few_kernel<HV, 4>), dim3((unsigned)q.batch), dim3(256), 0, q.stream, p);
@@ -956,19 +932,49 @@ const AttnVariant kMfma128d1 = {"bf16 attention head 128, 64 queries x 64-key st
                                 mfma_launch<1, 2, 4>};
 const AttnVariant kMfma128d2 = {"bf16 attention head 128, 64 queries x 64-key steps, prefetch 2, waves 4x1 mfma16", mfma_can_run<2>,
                                 mfma_launch<2, 2, 4>};
-// Two query blocks per wave pay when there are enough such workgroups, us with 2 / 1 (64-query workgroups):
-// head size 128: 32 x 2048^2 68 / 97, 256 x 128 x 512 18.5 / 22, 192 x 512^2 38.8 / 43.6, 40 x 1100^2 39.3 / 41.1, about even
-// at 96 x 512^2 (24.8 / 24.2) and 300 x 200 x 512 (36.2 / 35.4); one query per problem needs no second block
-// (256 x 1 x 2000: 45 / 39).  Head size 64: 32 x 2048^2 42 / 47, but 192 x 512^2 23.9 / 22.5, so in whole rounds only.
-bool wide_worthwhile_64(const AttnProblem &q) { return q.Lq > 16 && q.batch * ((q.Lq + 255) / 256) >= 230 && wide_rounds(q); }
-bool wide_worthwhile_128(const AttnProblem &q) { return q.Lq > 64 && q.batch * ((q.Lq + 127) / 128) >= 256; }
-const AttnVariant kMfma64wide = {"bf16 attention head 64, 128 or 256 queries x 64-key steps, prefetch 1, waves 4x1 or 8x1 of 32 queries, mfma16",
-                                 mfma_can_run<1>, wide_launch<1>, wide_worthwhile_64};
-const AttnVariant kMfma128wide = {"bf16 attention head 128, 128 or 256 queries x 64-key steps, prefetch 1, waves 4x1 or 8x1 of 32 queries, mfma16",
-                                  mfma_can_run<2>, wide_launch<2>, wide_worthwhile_128};
+// Eight waves per workgroup pay when there are enough such workgroups.  Head size 64: two of them per compute unit in (nearly)
+// whole rounds, us with 8 / 4 waves: 32 x 2048^2 40.5 / 44.4, 64 x 2048^2 81 / 87, 256 x 512^2 26.8 / 28.4, but 64 x 1100^2 (576
+// workgroups) 34.5 / 33.3, 300 x 384^2 (900) 24.6 / 22.1.  Head size 128: one per compute unit, 32 x 2048^2 70 / 84, 64 x 1100^2 57.7 /
+// 61.5, 128 x 512^2 (512) 25.2 / 29.9, 256 x 100 x 512 (256) 16.3 / 17.2; up to 64 queries half of their waves have none.
+bool whole_rounds(int64_t workgroups, int64_t round)
+{
+    return workgroups * 10 >= (workgroups + round - 1) / round * round * 9;
+}
+bool w8_worthwhile_64(const AttnProblem &q)
+{
+    const int64_t n = q.batch * ((q.Lq + 127) / 128);
+    return q.Lq > 64 && n >= 512 && whole_rounds(n, 512);
+}
+bool w8_worthwhile_128(const AttnProblem &q) { return q.Lq > 64 && q.batch * ((q.Lq + 127) / 128) >= 256; }
+
+// Head size 128: 256 queries a workgroup (attn_wide_kernel) over 2048 keys or more, where such workgroups fill whole rounds of the
+// compute units and pad no more queries than 128-query ones would.  Us with 256 / 128: 32 x 2048^2 66 / 70, 64 x 2048^2 131 / 137,
+// 8 x 8192^2 236 / 252, 32 x 2048 x 8192 240 / 254; 1024 keys 145 / 148 at 32 x 8192 in long runs and 150 / 139 in short ones,
+// 512 keys 192 x 2048 153 / 138; rounds that are not whole, 40 x 2048^2 119 / 95.
+bool wide_worthwhile(const AttnProblem &q)
+{
+    const int64_t n = q.batch * ((q.Lq + 255) / 256);
+    return q.Lk >= 2048 && 2 * ((q.Lq + 255) / 256) == (q.Lq + 127) / 128 && whole_rounds(n, 256);
+}
+
+hipError_t w8_launch_128(const AttnProblem &q)
+{
+    if (!wide_worthwhile(q)) return mfma_launch<1, 2, 8>(q);
+    AttnParams p = params_elements(q);
+    p.ldq *= 2; p.ldk *= 2; p.ldv *= 2;                  // bytes
+    p.strideQ *= 2; p.strideK *= 2; p.strideV *= 2;
+    const dim3 grid((unsigned)((q.Lq + 255) / 256), (unsigned)q.batch);
+    hipLaunchKernelGGL(attn_wide_kernel, grid, dim3(512), 0, q.stream, p);
+    return hipGetLastError();
+}
+
+const AttnVariant kMfma64w8 = {"bf16 attention head 64, 128 queries x 64-key steps, prefetch 1, waves 8x1 mfma16", mfma_can_run<1>,
+                               mfma_launch<1, 1, 8>, w8_worthwhile_64};
+const AttnVariant kMfma128w8 = {"bf16 attention head 128, 128 queries (256 over many keys) x 64-key steps, prefetch 1, waves 8x1 mfma16", mfma_can_run<2>,
+                                w8_launch_128, w8_worthwhile_128};
 // swept on the 96 x 512 x 512 x 64 workload: a prefetch distance of 1 is as fast as 2 (the step is bound
 // by its own dependency chain, not by load latency) and leaves more LDS free; 3 is slower
-const AttnVariant *const kBf16Table[] = {&kGeneral, &kMfma64d2, &kMfma64d1, &kMfma128d2, &kMfma128d1, &kMfma64wide, &kMfma128wide};   // the last that can run is the default
+const AttnVariant *const kBf16Table[] = {&kGeneral, &kMfma64d2, &kMfma64d1, &kMfma128d2, &kMfma128d1, &kMfma64w8, &kMfma128w8};   // the last that can run is the default
 
 }  // namespace
 
