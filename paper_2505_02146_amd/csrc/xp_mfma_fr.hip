@@ -232,41 +232,50 @@ bool fr_aligned(const Problem &q)
            q.strideA % epc == 0 && q.strideB % epc == 0;
 }
 
-// Microseconds: W from memory at 5 TB/s (8 out of the last-level cache), the fullest compute unit's loads of W and X at 45 KB a
-// microsecond (35 above 48 rows of X in several rounds: 60 x 12000 x 9000 92 us, 78 on the 64-row tile), 18 where rows start off a multiple of 4 bytes (64 x 8192 x 8192 37.7 us, 16 x 8191 x 8193 59 us)
-double fr_cost(const Problem &q)
-{
-    const double n = (double)(fr_swapped(q) ? q.M : q.N), m = (double)(fr_swapped(q) ? q.N : q.M), kb = (double)q.K * elem_size(q.in_type);
-    const int wb = fr_w_blocks((int64_t)n, (int64_t)m, q.batch);
-    const double per_cu = __builtin_ceil(__builtin_ceil(n / (8.0 * wb)) * q.batch / 256.0);
-    const double loads = per_cu * (8.0 * wb + fr_rows((int64_t)m)) * kb / (!fr_aligned(q) ? 18e3 : m > 48.0 && per_cu > 1.0 ? 35e3 : 45e3);
-    const double w_us = n * kb * q.batch / (n * kb * q.batch >= 6.7e7 ? 5e6 : 8e6);
-    return 4.0 + (loads > w_us ? loads : w_us);
-}
+// Chosen by few_rows_preferred, ahead of the table and the estimates: a call that it declines goes to another kernel.
+double fr_cost(const Problem &) { return 1e30; }
 
 const Variant kBfFr = {"bf16 few rows x 8 to 32 rows, eight waves split k, through registers, mfma16", fr_can_run<false>, fr_launch<false>, fr_cost};
 const Variant kI8Fr = {"i8 few rows x 8 to 32 rows, eight waves split k, through registers, mfma16", fr_can_run<true>, fr_launch<true>, fr_cost};
 
 }  // namespace
 
-// Whether the call is better off here than on a tile of 64 rows, whose compute units take 64 + 64 rows of K at 70 KB a
-// microsecond (40 where W does not fit the last-level cache, 30 where rows are not aligned) and W at 4.6 TB/s (8).
-// Measured us, here and there: 16 x 8192 x 8192 25 and 57, 16 x 4096 x 4096 7.8 and 18.7, 64 x 4096 x 4096 13.1 and 19.2,
-// 64 x 1024 x 16384 35 and 62; on the other side of the line 64 x 16384 x 2048 25 and 20, 32 x 16384 x 1024 10.7 and 7.8,
-// 64 x 8191 x 8193 89 and 71.  A K of less than a block for every wave and a
-// matrix-vector product with aligned rows (of any length) stay where they were.
+// Whether the call is better off here than on what else would run it.  Both sides were timed over 5400 calls (1 to 256
+// problems, bf16 and int8, 16 to 130000 rows of W, 64 bytes to 34 KB of K), with the operands from memory and with the
+// same ones over and over; the lines lie where the mean ratio of the times passes one.  What counts is how many 64-row
+// tiles of W there are (the other kernels have about a workgroup for each), how many rows of X share a load of W, and how
+// long K is.  Ratio here / there, operands from memory:
+//   up to 32 tiles   0.17 .. 0.97 up to 32 rows of X whatever K, up to 64 rows from 512 bytes on (below 1.0 .. 1.14)
+//   up to 64         0.25 .. 0.96 up to 16 rows, 0.4 .. 0.98 up to 32 from 256 bytes on, 0.5 .. 0.95 up to 64 from where the line is
+//   up to 128        0.4 .. 1.0 up to 16 rows, 0.55 .. 0.93 up to 32 from 1 KB, 0.6 .. 0.82 up to 48 from 2 KB, 0.6 .. 0.81 up to 64 from 4 KB
+//   one problem      its W are weights, which come from memory: up to 16 rows 0.57 .. 0.97 from 2 KB on; up to 48 rows 0.48 .. 0.91 where a
+//                    compute unit has at most one workgroup, 0.7 .. 0.9 to 192 tiles from 8 KB on and 0.75 .. 0.9 where two full rounds
+//                    stand against a second one there, else 1.0 .. 1.5
+// The operands of several problems are as a rule another kernel's results and still in the caches, where a tile kernel gains
+// more: 17 to 32 rows end at 128 tiles (beyond 1.1 .. 1.8), 33 to 48 at 64 (beyond 0.97 .. 1.6), 49 to 64 at 16 (32 problems 64 x 64 x
+// 4096 int8 12.6 us and 8.2), 9 to 16 at 128 and 8 at 256 (192 x 16 x 256 x 2048 int8 31.9 and 20.4, 128 x 4 x 256 x 2048 18 and 13.5)
+// -- unless W is more than the 256 MB last-level cache holds: up to 16 rows those have the lines of one problem (8 x 13 x 6872 x 4288
+// 76 and 107, 192 x 16 x 1024 x 1024 73 and 96).
+// 16 x 8192 x 8192 25 us here and 57, 16 x 4096 x 4096 7.8 and 18.7, 42 x 9266 x 11712 48 and 82; 192 problems 64 x 1024 x 64 97 and 15,
+// 96 problems 49 x 6144 x 48 297 and 27.  Rows off a 16-byte boundary (there: the any-alignment kernel) have the same lines
+// up to 128 tiles, and 0.78 .. 1.0 up to 16 rows and 256 tiles from 1 KB on.  A matrix-vector product with aligned rows (of
+// any length) has a kernel of its own.
 bool few_rows_preferred(const Problem &q)
 {
     if (q.in_type == XP_F32 || !(q.in_type == XP_BF16 ? fr_can_run<false>(q) : fr_can_run<true>(q))) return false;
-    const double n = (double)(fr_swapped(q) ? q.M : q.N), kb = (double)q.K * elem_size(q.in_type);
-    const bool aligned = fr_aligned(q);
     const int64_t epc = 16 / elem_size(q.in_type);
-    const bool gemv = q.N == 1 && (((uintptr_t)q.A | (uintptr_t)q.B) & 15) == 0 && q.a_sm % epc == 0 && q.strideA % epc == 0 && q.strideB % epc == 0;
-    if (kb < NW * BLOCKB || gemv) return false;
-    const bool cold = n * kb * q.batch >= 6.7e7;
-    const double loads = __builtin_ceil(__builtin_ceil(n / 64.0) * q.batch / 256.0) * 128.0 * kb / (!aligned ? 30e3 : cold ? 40e3 : 70e3);
-    const double w_us = n * kb * q.batch / (cold ? 4.6e6 : 8e6);
-    return fr_cost(q) <= 4.0 + (loads > w_us ? loads : w_us);
+    if (q.N == 1 && (((uintptr_t)q.A | (uintptr_t)q.B) & 15) == 0 && q.a_sm % epc == 0 && q.strideA % epc == 0 && q.strideB % epc == 0) return false;
+    const int64_t n = fr_swapped(q) ? q.M : q.N, m = fr_swapped(q) ? q.N : q.M, kb = q.K * elem_size(q.in_type);
+    const int64_t tiles = (n + 63) / 64 * q.batch;
+    const bool from_memory = n * kb * q.batch > 300000000;
+    if (q.batch > 1 && !(from_memory && m <= 16) && tiles > (m <= 8 ? 256 : m <= 32 ? 128 : m <= 48 ? 64 : 16)) return false;
+    if (tiles <= 32) return m <= 32 || kb >= 512;
+    if (tiles <= 64) return m <= 16 || kb >= (m <= 32 ? 256 : m <= 48 ? 1024 : 4096);
+    if (tiles <= 128) return m <= 16 || kb >= (m <= 32 ? 1024 : m <= 48 ? 2048 : 4096);
+    if (!fr_aligned(q)) return tiles <= 256 && m <= 16 && kb >= 1024;
+    if (m <= 16) return kb >= (m <= 8 && tiles <= 256 ? 1024 : tiles <= 1024 || q.batch > 1 ? 2048 : 4096);
+    const int64_t rows = 8 * fr_w_blocks(n, m, 1), workgroups = (n + rows - 1) / rows;
+    return m <= 48 && kb >= 4096 && (workgroups <= 256 || (kb >= 8192 && tiles <= 192) || (m <= 32 && tiles > 256 && workgroups <= 512));
 }
 
 int fr_variants(xp_dtype in_type, const Variant **out)

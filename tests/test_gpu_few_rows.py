@@ -91,3 +91,23 @@ def test_few_rows_splits(xp, oracle, kind, few, many, K):
         assert np.array_equal(c.cpu().numpy(), ref)
     else:
         check_float(c.cpu().numpy(), ref, f"{few}x{many}x{K}")
+
+
+@pytest.mark.parametrize("kind", ["bf16", "i8"])
+@pytest.mark.parametrize("few", [3, 17])
+def test_few_rows_of_a_streamed_matrix(xp, oracle, kind, few):
+    """W of 64 MB and more takes loads of its own; odd K, a ragged last workgroup."""
+    many, K = 8201, 8209 if kind == "i8" else 4105
+    assert many * K * (1 if kind == "i8" else 2) >= 64 << 20
+    import torch
+    make = (lambda s, t: inputs.int8_uniform(s, 1, t)) if kind == "i8" else (lambda s, t: inputs.to_bf16_bits(inputs.normal(s, 1, t)))
+    A, B = make((few, K), 1), make((many, K), 2)
+    ref = oracle.gemm_i8(few, many, K, A.reshape(-1), "row", B.reshape(-1), "col") if kind == "i8" else oracle.gemm_float(few, many, K, A.reshape(-1), "row", B.reshape(-1), "col")
+    c = torch.full((few, many), 7, dtype=torch.int32 if kind == "i8" else torch.float32, device="cuda")
+    xp.xp_force_config(0, kind, _variant(xp, 0, kind, "few rows"))
+    xp.xp_gemm(few, many, K, 1.0, dev(A.reshape(-1)), "row", K, dev(B.reshape(-1)), "col", K, 0.0, c, "row", many, a_type=kind, b_type=kind)
+    xp.xp_force_config(0, kind, -1)
+    if kind == "i8":
+        assert np.array_equal(c.cpu().numpy(), ref)
+    else:
+        check_float(c.cpu().numpy(), ref, f"{few}x{many}x{K}")

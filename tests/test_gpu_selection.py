@@ -1,0 +1,44 @@
+"""Which kernel the library picks where several can run the call: lines that were measured on both sides (the figures stand
+beside the rules), asked with real buffers."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def xp():
+    from paper_2505_02146_amd import xp as m
+    for op in (0, 1, 2):
+        for t in ("f32", "bf16", "i8"):
+            m.xp_force_config(op, t, -1)
+    return m
+
+
+_TORCH = {"f32": "float32", "bf16": "bfloat16", "i8": "int8"}
+
+
+def _gemm(xp, kind, batch, M, N, K, la="row", lb="col", skew=0):
+    """The name of the kernel that a product with operands `skew` elements past an aligned address ran on."""
+    import torch
+    n = max(batch, 1)
+    a, b = (torch.zeros(n * r * K + skew, dtype=getattr(torch, _TORCH[kind]), device="cuda")[skew:] for r in (M, N))
+    c = torch.full((n * M * N,), 7, dtype=torch.int32 if kind == "i8" else torch.float32, device="cuda")
+    lda, ldb = (K if la == "row" else M), (N if lb == "row" else K)
+    if batch == 0:
+        xp.xp_gemm(M, N, K, 1.0, a, la, lda, b, lb, ldb, 0.0, c, "row", N)
+    else:
+        xp.xp_gemm_batched(batch, M, N, K, 1.0, a, la, lda, M * K, b, lb, ldb, N * K, 0.0, c, "row", N, M * N)
+    assert not c.any(), "zeros times zeros"
+    op = 0 if batch == 0 else 1
+    return xp.xp_describe_config(op, kind, xp.xp_last_config(op, kind))
+
+
+@pytest.mark.parametrize("kind", ["bf16", "i8"])
+@pytest.mark.parametrize("call,few", [
+    ((0, 16, 8192, 2048), True), ((0, 64, 4096, 4096), True), ((0, 40, 2560, 8192), True), ((0, 20, 10240, 4096), True), ((2, 4, 1024, 1024), True),
+    # many problems: a workgroup per 64-row tile of the other kernels is more than the chip holds at once
+    ((96, 64, 687, 32), False), ((192, 64, 1024, 64), False), ((96, 49, 6144, 48), False), ((32, 33, 4096, 512), False),
+    ((128, 17, 256, 2048), False), ((128, 1024, 7, 64), False), ((128, 64, 64, 4096), False), ((0, 64, 16384, 2048), False),
+])
+def test_few_rows(xp, kind, call, few):
+    assert ("few rows" in _gemm(xp, kind, *call)) == few
