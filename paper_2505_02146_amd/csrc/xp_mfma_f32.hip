@@ -626,14 +626,18 @@ hipError_t f32s_launch(const Problem &q)
 // per chunk of 256 k (256^3 4.4 us, 512 x 512 x 1024 11.2 us, 64 x 64 x 4096 33 us, each ahead of the tiled kernels:
 // 8.4, 26.5, 97). One element per load: 3 us and 4.5 us per chunk. With more than one workgroup per compute unit the
 // pipelined tiled kernels win (1024^2 x 256: 11.0 against 9.3).  Those want aligned operands; the ones left for the others
-// load element by element and lose there too: 61 x 1021 x 130 4.95 us here and 8.9, 333 x 999 x 271 11.4 and 14.7,
-// 1001 x 1003 x 1005 36 (along k; 40 mixed) and 47, 1023 x 500 x 1023 22.8 and 47; even at 700 x 701 x 64, where they stay.
+// load element by element and lose to two workgroups per compute unit and more, whatever K: 61 x 1021 x 130 4.95 us here and 8.9,
+// 333 x 999 x 271 11.4 and 14.7, 1023 x 500 x 1023 22.8 and 47, 257 x 255 x 20001 246 and 857.  To four per compute unit it
+// takes a K of more than two chunks: 1001 x 1003 x 1005 36 and 47, 356 x 1984 x 720 29.6 and 33.8, but 132 x 4926 x 376 23.6 and 19.7;
+// beyond, a workgroup's loads, which nothing overlaps, cost more: 2001 x 2003 x 2005 306 and 228, 4001 x 4003 x 4005 2432 and
+// 1360, 48 problems 112 x 569 x 250 51 and 35 (1501 x 1503 x 1505, 121 .. 138 and 174, is the exception: 144 of the 128x128 tiles).
 double f32s_cost(const Problem &q)
 {
     const double tiles = (double)((q.M + ST - 1) / ST) * (double)((q.N + ST - 1) / ST) * (double)q.batch;
     const double chunks = (double)((q.K + SK - 1) / SK);
     if (f32s_form(q, true) && f32s_form(q, false)) return tiles > 256.0 || q.K > 8192 ? 1e30 : 2.4 + 2.0 * chunks;
     if (!f32s_form_any(q, true) || !f32s_form_any(q, false)) return tiles > 256.0 || q.K > 8192 ? 1e30 : 3.0 + 4.5 * chunks;
+    if (tiles > (q.K > 512 ? 1024.0 : 512.0)) return 1e30;
     return 2.4 + 2.4 * chunks * (tiles <= 256.0 ? 1.0 : 0.7 * tiles / 256.0);
 }
 

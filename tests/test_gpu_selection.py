@@ -42,3 +42,13 @@ def _gemm(xp, kind, batch, M, N, K, la="row", lb="col", skew=0):
 ])
 def test_few_rows(xp, kind, call, few):
     assert ("few rows" in _gemm(xp, kind, *call)) == few
+
+
+@pytest.mark.parametrize("call,small", [
+    ((0, 61, 1021, 130), True), ((0, 257, 255, 20001), True), ((0, 1001, 1003, 1005), True), ((0, 500, 1001, 377), True),
+    ((0, 132, 4926, 377), False), ((0, 2001, 2003, 701), False), ((48, 112, 569, 251), False), ((0, 4001, 4003, 129), False),
+])
+@pytest.mark.parametrize("la,lb", [("row", "col"), ("row", "row"), ("col", "col")])
+def test_fp32_kernel_for_small_products(xp, call, small, la, lb):
+    """Operands of any alignment: 32x32 tiles up to four per compute unit, the tiled kernels beyond."""
+    assert ("four waves split k" in _gemm(xp, "f32", *call, la=la, lb=lb, skew=1)) == small
