@@ -52,3 +52,21 @@ def test_few_rows(xp, kind, call, few):
 def test_fp32_kernel_for_small_products(xp, call, small, la, lb):
     """Operands of any alignment: 32x32 tiles up to four per compute unit, the tiled kernels beyond."""
     assert ("four waves split k" in _gemm(xp, "f32", *call, la=la, lb=lb, skew=1)) == small
+
+
+@pytest.mark.parametrize("call,any_alignment", [
+    # N, H, W, Cin, Cout, R, S, stride, pad
+    ((6, 7, 7, 256, 32, 11, 11, 1, 5), False), ((2, 1, 1434, 64, 32, 1, 40, 2, 0), False), ((1, 28, 28, 64, 176, 7, 7, 2, 3), False),
+    ((1, 28, 28, 32, 176, 7, 7, 2, 3), True),            # 64-byte pixels and more than 32 taps
+    ((1, 28, 28, 72, 176, 7, 7, 2, 3), True), ((1, 28, 28, 64, 176, 3, 3, 1, 1), False),
+])
+def test_convolutions_of_many_taps(xp, call, any_alignment):
+    import torch
+    n, h, w, ci, co, r, s, st, p = call
+    x, f = (torch.zeros(e, dtype=torch.bfloat16, device="cuda") for e in (n * h * w * ci, co * r * s * ci))
+    ph, pw = (p, p) if h > 1 else (0, p)
+    P, Q = (h + 2 * ph - r) // st + 1, (w + 2 * pw - s) // st + 1
+    out = torch.full((n * P * Q * co,), 7.0, device="cuda")
+    xp.xp_conv2d_nhwc(n, h, w, ci, co, r, s, st, st, ph, pw, x, f, "krsc", out)
+    assert not out.any()
+    assert ("any alignment" in xp.xp_describe_config(2, "bf16", xp.xp_last_config(2, "bf16"))) == any_alignment
