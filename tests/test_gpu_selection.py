@@ -54,6 +54,19 @@ def test_fp32_kernel_for_small_products(xp, call, small, la, lb):
     assert ("four waves split k" in _gemm(xp, "f32", *call, la=la, lb=lb, skew=1)) == small
 
 
+def _conv(xp, call, layout="krsc"):
+    """The name of the kernel that a convolution ran on (N, H, W, Cin, Cout, R, S, stride, pad)."""
+    import torch
+    n, h, w, ci, co, r, s, st, p = call
+    x, f = (torch.zeros(e, dtype=torch.bfloat16, device="cuda") for e in (n * h * w * ci, co * r * s * ci))
+    ph, pw = (p, p) if h > 1 else (0, p)
+    P, Q = (h + 2 * ph - r) // st + 1, (w + 2 * pw - s) // st + 1
+    out = torch.full((n * P * Q * co,), 7.0, device="cuda")
+    xp.xp_conv2d_nhwc(n, h, w, ci, co, r, s, st, st, ph, pw, x, f, layout, out)
+    assert not out.any()
+    return xp.xp_describe_config(2, "bf16", xp.xp_last_config(2, "bf16"))
+
+
 @pytest.mark.parametrize("call,any_alignment", [
     # N, H, W, Cin, Cout, R, S, stride, pad
     ((6, 7, 7, 256, 32, 11, 11, 1, 5), False), ((2, 1, 1434, 64, 32, 1, 40, 2, 0), False), ((1, 28, 28, 64, 176, 7, 7, 2, 3), False),
@@ -61,12 +74,16 @@ def test_fp32_kernel_for_small_products(xp, call, small, la, lb):
     ((1, 28, 28, 72, 176, 7, 7, 2, 3), True), ((1, 28, 28, 64, 176, 3, 3, 1, 1), False),
 ])
 def test_convolutions_of_many_taps(xp, call, any_alignment):
-    import torch
-    n, h, w, ci, co, r, s, st, p = call
-    x, f = (torch.zeros(e, dtype=torch.bfloat16, device="cuda") for e in (n * h * w * ci, co * r * s * ci))
-    ph, pw = (p, p) if h > 1 else (0, p)
-    P, Q = (h + 2 * ph - r) // st + 1, (w + 2 * pw - s) // st + 1
-    out = torch.full((n * P * Q * co,), 7.0, device="cuda")
-    xp.xp_conv2d_nhwc(n, h, w, ci, co, r, s, st, st, ph, pw, x, f, "krsc", out)
-    assert not out.any()
-    assert ("any alignment" in xp.xp_describe_config(2, "bf16", xp.xp_last_config(2, "bf16"))) == any_alignment
+    assert ("any alignment" in _conv(xp, call)) == any_alignment
+
+
+@pytest.mark.parametrize("call,layout,few", [
+    ((8, 224, 224, 3, 64, 7, 7, 2, 3), "krsc", True), ((2, 224, 224, 3, 64, 3, 3, 1, 1), "krsc", True),
+    ((8, 224, 224, 3, 64, 7, 7, 2, 3), "rsck", False), ((16, 120, 120, 3, 32, 3, 3, 1, 1), "rsck", True),
+    ((2, 37, 30, 3, 64, 7, 7, 2, 3), "krsc", False), ((2, 60, 60, 3, 4, 3, 3, 1, 1), "rsck", True),
+    ((2, 1, 7427, 1, 128, 1, 15, 1, 0), "krsc", False), ((9, 1, 20066, 1, 4, 1, 40, 1, 0), "krsc", False),
+    ((4, 1, 4261, 2, 4, 1, 3, 1, 0), "rsck", False), ((19, 1, 4930, 7, 4, 1, 15, 2, 0), "rsck", True),
+    ((34, 1, 20000, 6, 8, 1, 5, 2, 0), "krsc", True), ((14, 1, 33664, 1, 16, 1, 1, 1, 0), "krsc", False),
+])
+def test_convolutions_of_few_channels(xp, call, layout, few):
+    assert ("few input channels" in _conv(xp, call, layout)) == few
