@@ -286,8 +286,9 @@ xp_status xp_depthwise_conv2d_nhwc(int64_t N, int64_t H, int64_t W, int64_t C, i
  *      warm-up launches) and the three fastest twice more, in turn; reward = 1 / best time if
  *      valid, else 0; the largest reward wins;
  *   4. records the winner for the call's shape (operator, type, batch, M, N, K, which operands are
- *      contiguous along K, and for a convolution its geometry), so that every later call of that
- *      shape uses it (ahead of the built-in table), and computes C once more with the winner.
+ *      contiguous along K, which of their bases, pitches and batch strides are no multiple of 16
+ *      bytes, and for a convolution its geometry), so that every later call of that shape uses it
+ *      (ahead of the built-in table), and computes C once more with the winner.
  * The calls synchronise `stream` many times and are meant to be made once per shape, off the
  * critical path.  C must hold valid input when beta != 0; it ends up holding the result.
  *   workspace        DEVICE memory owned by the caller, 256-byte aligned, at least

@@ -184,13 +184,13 @@ int select_uncached(const Problem &q)
 }
 
 // Programs call the same few shapes over and over, and a table walk costs microseconds that a small
-// kernel does not have: each thread remembers its last selections.  A remembered variant is used
-// only if it can still run this call (alignment and pitches are not part of the key); changes of the
-// run-time table invalidate everything through the generation count.
+// kernel does not have: each thread remembers its last selections, under everything that choosing reads: the shape and which
+// of its 16-byte boundaries the operands keep.  A remembered variant is used only if it can still run this call (pitches
+// themselves are not part of the key); changes of the run-time table invalidate everything through the generation count.
 std::atomic<unsigned> g_generation{1};
 
 struct SelKey {
-    int64_t op, type, kc, batch, M, N, K, planar;
+    int64_t op, type, kc, batch, M, N, K, planar, misaligned;
     int64_t geom[9];                                      // convolution: H, W, Cin, R, S, strides, pads (the run-time table is keyed on them too)
     bool operator==(const SelKey &o) const { return memcmp(this, &o, sizeof *this) == 0; }
 };
@@ -207,10 +207,11 @@ int select_variant(const Problem &q)
     SelKey k;
     k.op = q.op; k.type = q.in_type; k.kc = ((q.conv || q.a_sk == 1) ? 1 : 0) | (q.b_sk == 1 ? 2 : 0);
     k.batch = q.batch; k.M = q.M; k.N = q.N; k.K = q.K; k.planar = q.c_plane != 0;
+    k.misaligned = misaligned_bits(q);
     const int64_t geom[9] = {q.H, q.W, q.Cin, q.R, q.S, q.sh, q.sw, q.ph, q.pw};
     for (int i = 0; i < 9; ++i) k.geom[i] = q.conv ? geom[i] : 0;
     uint64_t h = 1469598103934665603ull;
-    for (const int64_t w : {k.op, k.type, k.kc, k.batch, k.M, k.N, k.K, k.planar}) { h ^= (uint64_t)w; h *= 1099511628211ull; }
+    for (const int64_t w : {k.op, k.type, k.kc, k.batch, k.M, k.N, k.K, k.planar, k.misaligned}) { h ^= (uint64_t)w; h *= 1099511628211ull; }
     for (const int64_t w : k.geom) { h ^= (uint64_t)w; h *= 1099511628211ull; }
     SelSlot &slot = cache[(h >> 20) % SLOTS];
     const unsigned gen = g_generation.load(std::memory_order_acquire);

@@ -154,4 +154,16 @@ __device__ __forceinline__ unsigned xcd_chunked(unsigned linear, unsigned grid)
 
 inline int elem_size(xp_dtype t) { return t == XP_F32 || t == XP_I32 ? 4 : (t == XP_BF16 ? 2 : 1); }
 
+// What of a call's operands is no multiple of 16 bytes, one bit each: base, pitch and batch stride of A, then of B.  Kernels
+// decline by it, and where several can run, the rules and estimates that choose among them read it: it belongs to every key
+// under which a choice is remembered.
+inline int misaligned_bits(const Problem &q)
+{
+    const int64_t below = 16 / elem_size(q.in_type) - 1;                 // (a power of two less one)
+    auto bits = [&](const void *p, int64_t s_k, int64_t s_outer, int64_t stride) {
+        return ((uintptr_t)p % 16 != 0 ? 1 : 0) | (((s_k == 1 ? s_outer : s_k) & below) != 0 ? 2 : 0) | ((stride & below) != 0 ? 4 : 0);
+    };
+    return (q.conv ? ((uintptr_t)q.A % 16 != 0 ? 1 : 0) : bits(q.A, q.a_sk, q.a_sm, q.strideA)) | bits(q.B, q.b_sk, q.b_sn, q.strideB) << 3;
+}
+
 }  // namespace xp

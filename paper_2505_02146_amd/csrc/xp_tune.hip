@@ -10,6 +10,7 @@
 #include "xp_internal.hpp"
 
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -52,6 +53,7 @@ FastKey fast_key(const Problem &q)
     } else {
         k.v[3] = q.batch; k.v[4] = q.M; k.v[5] = q.N; k.v[6] = q.K; k.v[7] = a_kc;
     }
+    k.v[15] = misaligned_bits(q);
     return k;
 }
 
@@ -61,6 +63,8 @@ bool parse_key(const char *text, FastKey *k, xp_dtype *type)
     memset(k, 0, sizeof *k);
     long long c[12];
     int t, op, a, b;
+    const char *u = strstr(text, " u");                     // which 16-byte boundaries the operands do not keep; none if it is missing
+    if (u) k->v[15] = strtoll(u + 2, nullptr, 10);
     if (sscanf(text, "conv t%d n%lld h%lld w%lld c%lld k%lld r%lld s%lld sh%lld sw%lld ph%lld pw%lld b%d", &t, &c[0], &c[1], &c[2],
                &c[3], &c[4], &c[5], &c[6], &c[7], &c[8], &c[9], &c[10], &b) == 13) {
         k->v[0] = -1; k->v[1] = t; k->v[2] = b;
@@ -78,8 +82,9 @@ bool parse_key(const char *text, FastKey *k, xp_dtype *type)
 
 std::string shape_key(const Problem &q)
 {
-    char buf[256];
+    char buf[256], misaligned[16] = "";
     const int a_kc = (q.conv || q.a_sk == 1) ? 1 : 0, b_kc = q.b_sk == 1 ? 1 : 0;
+    if (misaligned_bits(q) != 0) snprintf(misaligned, sizeof misaligned, " u%d", misaligned_bits(q));
     if (q.conv)
         snprintf(buf, sizeof buf, "conv t%d n%lld h%lld w%lld c%lld k%lld r%lld s%lld sh%lld sw%lld ph%lld pw%lld b%d",
                  (int)q.in_type, (long long)(q.M / (q.P * q.Q)), (long long)q.H, (long long)q.W, (long long)q.Cin,
@@ -88,7 +93,7 @@ std::string shape_key(const Problem &q)
     else
         snprintf(buf, sizeof buf, "gemm%d t%d b%lld m%lld n%lld k%lld a%d b%d", (int)q.op, (int)q.in_type,
                  (long long)q.batch, (long long)q.M, (long long)q.N, (long long)q.K, a_kc, b_kc);
-    return buf;
+    return std::string(buf) + misaligned;
 }
 
 int variant_by_name(xp_dtype t, const std::string &name)
@@ -257,7 +262,12 @@ int runtime_tuned_variant(const Problem &q)
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         if (g_fast.empty()) return -1;
-        auto it = g_fast.find(fast_key(q));
+        FastKey k = fast_key(q);
+        auto it = g_fast.find(k);
+        if (it == g_fast.end() && k.v[15] != 0) {            // an entry for the shape alone: aligned operands, or a file that tells no more
+            k.v[15] = 0;
+            it = g_fast.find(k);
+        }
         if (it == g_fast.end()) return -1;
         v = it->second;
     }

@@ -87,3 +87,50 @@ def test_convolutions_of_many_taps(xp, call, any_alignment):
 ])
 def test_convolutions_of_few_channels(xp, call, layout, few):
     assert ("few input channels" in _conv(xp, call, layout)) == few
+
+
+def _fresh(call):
+    """`call` in a thread of its own, which remembers no selection."""
+    import threading
+    box = []
+    t = threading.Thread(target=lambda: box.append(call()))
+    t.start()
+    t.join()
+    return box[0]
+
+
+@pytest.mark.parametrize("kind,call,la,lb", [
+    ("bf16", (0, 512, 384, 512), "row", "col"), ("bf16", (0, 512, 384, 512), "row", "row"), ("i8", (0, 512, 384, 512), "row", "col"),
+    ("bf16", (0, 5120, 1, 1024), "row", "col"), ("bf16", (0, 32, 10240, 4096), "row", "col"), ("f32", (0, 768, 512, 512), "row", "col"),
+    ("bf16", (3, 256, 128, 256), "row", "col"),
+])
+def test_a_remembered_choice_is_for_its_alignment_only(xp, kind, call, la, lb):
+    """Misaligned operands, then aligned ones of the same shape, and the other way round: what a first call would run."""
+    aligned, off = (_fresh(lambda s=s: _gemm(xp, kind, *call, la=la, lb=lb, skew=s)) for s in (0, 1))
+    assert aligned != off, "the case is meant to be one where alignment decides"
+    for skew in (1, 0, 1, 1, 0, 0):
+        assert _gemm(xp, kind, *call, la=la, lb=lb, skew=skew) == (off if skew else aligned), skew
+
+
+def test_a_tuned_choice_is_for_its_alignment_only(xp, tmp_path):
+    import torch
+    M, N, K = 512, 384, 512
+    xp.xp_tune_clear()
+    aligned = _fresh(lambda: _gemm(xp, "bf16", 0, M, N, K))
+    ws = torch.empty(xp.xp_tune_workspace_bytes(M * N), dtype=torch.uint8, device="cuda")
+    a, b = (torch.randn(r * K + 1, device="cuda").bfloat16()[1:] for r in (M, N))
+    c = torch.zeros(M * N, device="cuda")
+    won, _ = xp.xp_tune_gemm(M, N, K, 1.0, a, "row", K, b, "col", K, 0.0, c, "row", N, ws, reps=3)
+    off = xp.xp_describe_config(0, "bf16", won)
+    for _ in range(2):                                       # from the table, then from the file
+        assert _gemm(xp, "bf16", 0, M, N, K) == aligned and _gemm(xp, "bf16", 0, M, N, K, skew=1) == off
+        xp.xp_tune_save(tmp_path / "t.txt")
+        xp.xp_tune_clear()
+        xp.xp_tune_load(tmp_path / "t.txt")
+    # an entry that names the shape alone serves every alignment whose call its variant can run
+    general = xp.xp_describe_config(0, "bf16", 0)
+    (tmp_path / "old.txt").write_text(f"gemm0 t1 b1 m{M} n{N} k{K} a1 b1 | {general}\n")
+    xp.xp_tune_clear()
+    xp.xp_tune_load(tmp_path / "old.txt")
+    assert _gemm(xp, "bf16", 0, M, N, K) == general and _gemm(xp, "bf16", 0, M, N, K, skew=1) == general
+    xp.xp_tune_clear()
