@@ -282,8 +282,8 @@ hipError_t fl_launch(const Problem &q)
 // Below 8 channels it is the choice from about 90000 output pixels on: up to there its start, some 5 us for the filter and the
 // first tile, costs more than the reuse saves (both sides timed over 1800 calls; pixels, time here over that of the any-alignment
 // kernel: 8000 1.2 .. 1.3, 50000 1.3, 80000 .. 100000 0.93 .. 1.04, 130000 0.64 .. 1.0; 247000 22 us and 39, the first layer's
-// 401408 29 and 56, 516128 17 and 40).  A filter along its output channels is gathered element by element at the start and
-// takes twice as many.  Four output rows or fewer leave waves of a tile without work, and long rows of few elements leave
+// 401408 29 and 56, 516128 17 and 40), above 128 output channels from 50000 on (75264 x 448 30 us and 43, 20000 1.3).  A filter
+// along its output channels is gathered element by element at the start and takes twice as many.  Four output rows or fewer leave waves of a tile without work, and long rows of few elements leave
 // few tiles: there it takes 250000 pixels and a tile for every compute unit (47 x 1 x 27594 x 6 -> 8, 5 taps 24 us and 48, but
 // 2 x 1 x 7427 x 1 -> 128, 15 taps, a tile per image, 56 and 6.3, 14 x 1 x 33664 x 1 -> 16, one tap, 67 and 36).  Where the any-alignment
 // kernel declines (fewer than 8 channels, filter along them) the other side is the general kernel: 0.2 .. 0.85 of its time
@@ -295,7 +295,7 @@ double fl_cost(const Problem &q)
     if (q.b_sk != 1 && q.N < 8) {
         chosen = q.P > 4 || q.K >= 24;
     } else if (q.P > 4) {
-        chosen = q.M >= (q.b_sk == 1 ? 90000 : 200000);
+        chosen = q.M >= (q.N > 128 ? 50000 : 90000) * (q.b_sk == 1 ? 1 : 2);
     } else {
         FlTile t;
         chosen = q.M >= 250000 && fl_tile(q, &t) && q.M / (q.P * q.Q) * ((q.P + t.TP - 1) / t.TP) * ((q.Q + 16 * t.GQ - 1) / (16 * t.GQ)) *

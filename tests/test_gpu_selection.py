@@ -83,6 +83,7 @@ def test_convolutions_of_many_taps(xp, call, any_alignment):
     ((2, 37, 30, 3, 64, 7, 7, 2, 3), "krsc", False), ((2, 60, 60, 3, 4, 3, 3, 1, 1), "rsck", True),
     ((2, 1, 7427, 1, 128, 1, 15, 1, 0), "krsc", False), ((9, 1, 20066, 1, 4, 1, 40, 1, 0), "krsc", False),
     ((4, 1, 4261, 2, 4, 1, 3, 1, 0), "rsck", False), ((19, 1, 4930, 7, 4, 1, 15, 2, 0), "rsck", True),
+    ((16, 60, 60, 6, 448, 3, 3, 1, 1), "krsc", True), ((16, 60, 60, 6, 448, 3, 3, 1, 1), "rsck", False),
     ((34, 1, 20000, 6, 8, 1, 5, 2, 0), "krsc", True), ((14, 1, 33664, 1, 16, 1, 1, 1, 0), "krsc", False),
 ])
 def test_convolutions_of_few_channels(xp, call, layout, few):
