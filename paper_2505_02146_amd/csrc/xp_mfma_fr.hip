@@ -235,8 +235,8 @@ bool fr_aligned(const Problem &q)
 // Chosen by few_rows_preferred, ahead of the table and the estimates: a call that it declines goes to another kernel.
 double fr_cost(const Problem &) { return 1e30; }
 
-const Variant kBfFr = {"bf16 few rows x 8 to 32 rows, eight waves split k, through registers, mfma16", fr_can_run<false>, fr_launch<false>, fr_cost};
-const Variant kI8Fr = {"i8 few rows x 8 to 32 rows, eight waves split k, through registers, mfma16", fr_can_run<true>, fr_launch<true>, fr_cost};
+const Variant kBfFr = {"bf16 few rows x 8 to 40 rows, eight waves split k, through registers, mfma16", fr_can_run<false>, fr_launch<false>, fr_cost};
+const Variant kI8Fr = {"i8 few rows x 8 to 40 rows, eight waves split k, through registers, mfma16", fr_can_run<true>, fr_launch<true>, fr_cost};
 
 }  // namespace
 

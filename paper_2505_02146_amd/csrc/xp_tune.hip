@@ -96,8 +96,10 @@ std::string shape_key(const Problem &q)
     return std::string(buf) + misaligned;
 }
 
-int variant_by_name(xp_dtype t, const std::string &name)
+int variant_by_name(xp_dtype t, std::string name)
 {
+    const size_t old = name.find("few rows x 8 to 32 rows");     // the name before it had workgroups of 40 rows, in tables saved then
+    if (old != std::string::npos) name.replace(old, 23, "few rows x 8 to 40 rows");
     const int n = num_variants(t);
     for (int i = 0; i < n; ++i)
         if (name == variant(t, i)->name) return i;

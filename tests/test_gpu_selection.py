@@ -134,4 +134,9 @@ def test_a_tuned_choice_is_for_its_alignment_only(xp, tmp_path):
     xp.xp_tune_clear()
     xp.xp_tune_load(tmp_path / "old.txt")
     assert _gemm(xp, "bf16", 0, M, N, K) == general and _gemm(xp, "bf16", 0, M, N, K, skew=1) == general
+    # a name that has changed since
+    (tmp_path / "old.txt").write_text("gemm0 t1 b1 m40 n16384 k520 a1 b1 | bf16 few rows x 8 to 32 rows, eight waves split k, through registers, mfma16\n")
+    assert "few rows" not in _fresh(lambda: _gemm(xp, "bf16", 0, 40, 16384, 520))
+    xp.xp_tune_load(tmp_path / "old.txt")
+    assert "few rows" in _gemm(xp, "bf16", 0, 40, 16384, 520)
     xp.xp_tune_clear()
