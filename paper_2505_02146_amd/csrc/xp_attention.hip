@@ -7,8 +7,11 @@
 //
 // The kernels:
 //   general   one wave per query, fp32 VALU arithmetic, any head size, fp32 or bf16 inputs
-//   mfma      bf16 inputs, head size 64 for Q/K and for V: both contractions on the 16x16x32
-//             matrix-core instruction, laid out so that nothing has to be transposed between them
+//   mfma      bf16 inputs, head size 64 or 128 for Q/K and for V: both contractions on the 16x16x32
+//             matrix-core instruction, laid out so that nothing has to be transposed between them;
+//             four or eight waves per workgroup
+//   wide      the same for 32 queries per wave: long sequences at head size 128
+//   few       the same for at most 16 queries, where the waves share out the keys
 #include "xp_internal.hpp"
 #include "xp_lds_tr.hpp"
 
@@ -626,10 +629,10 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(AttnParams p)
 // soon as its products are, so that 64 KB or more per compute unit are always on their way.  At the end the waves' sums
 // meet in LDS, scaled to the largest of their maxima.  256 x 1 x 2000 x 128 54 -> 46 us (5.7 TB/s); 16 x 1 x 8192 x 128 119 ->
 // 43 us, where 16 compute units take 98 KB a microsecond each.
-// Every wave starts from the same reference maximum, that of the first 64 keys, whose scores four waves compute from
-// registers while the first tiles are on their way: probabilities are rounded to bf16 against the reference that the other
+// Every wave starts from the same reference maximum, that of the first 64 keys, which are the first tiles of one or two waves: the
+// waves meet once, after their first scores.  Probabilities are then rounded to bf16 against the reference that the other
 // kernels would hold, so that a query's result does not depend on how many queries are asked for with it (with references of
-// the waves' own it moved by 2e-3, two independent roundings; 40 x 1 x 300 x 128 takes 6.2 us for it instead of 6.0).
+// the waves' own it moved by 2e-3, two independent roundings).
 // Layouts and steps are those of the kernels above, with tiles of 64 / HV keys.
 template <int HV, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
@@ -638,10 +641,9 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
     constexpr int HALF = TK * KROW, KT = HALF * HV, REGION = 2 * KT;   // 16 KB per wave
     constexpr int LPT = KT / 1024;                       // loads per K or V tile
     constexpr int KB = TK / 16, HS = TK / 32;
-    static_assert(NW >= 4, "four waves score the first 64 keys");
     // (one array: with a second one the compiler tells them apart and waits for all loads into LDS before each read from the tiles)
-    __shared__ __attribute__((aligned(1024))) char lds[NW * REGION + 16 * 16 * 4];
-    float *const first_top = (float *)(lds + NW * REGION);   // [query][wave, g]: largest scaled score of 4 of the first 64 keys
+    __shared__ __attribute__((aligned(1024))) char lds[NW * REGION + HV * 16 * 16];
+    float *const first_top = (float *)(lds + NW * REGION);   // [tile][query][g]: largest scaled scores of the first 64 keys
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -659,15 +661,13 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
 #pragma unroll
     for (int s = 0; s < 2 * HV; ++s)
         qf[s] = __builtin_amdgcn_raw_buffer_load_b128(rq, r < p.Lq ? (unsigned)(r * p.ldq) + (32 * s + 8 * g) * 2 : OOB, 0, 0);
-    u32x4 kf0[2 * HV];                                   // 16 of the first 64 keys (a call with fewer does not come here); waves 4 to 7 load none
-#pragma unroll
-    for (int s = 0; s < 2 * HV; ++s)
-        kf0[s] = __builtin_amdgcn_raw_buffer_load_b128(rk, wave < 4 ? (unsigned)((wave * 16 + r) * ldk) + (32 * s + 8 * g) * 2 : OOB, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);                   // ahead of the tiles: the wait for them leaves the tiles' loads outstanding
 
-    // the wave's tiles: a contiguous share
+    // the wave's tiles: a contiguous share, but for tile 1 at head size 128, which changes places with the second wave's first
+    // (with loads of their own for the 64 keys one decoding step of 256 x 1 x 2000 x 128 took 46.8 us, with this 46.4)
     const int NT = (Lk + TK - 1) / TK;
     const int first = (int)((long long)NT * wave / NW), last = (int)((long long)NT * (wave + 1) / NW);
+    const int second = HV == 2 ? (int)((long long)NT / NW) : 1;
+    auto tile = [&](int t) __attribute__((always_inline)) { return t == 1 ? second : t == second ? 1 : t; };
 
     const int krow = lane >> 3;
     const int kchunk = ((lane & 7) ^ (krow & 6)) << 4;
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
         for (int hv = 0; hv < HV; ++hv)
 #pragma unroll
             for (int i = 0; i < TK / 8; ++i) {
-                const unsigned off = t < last ? (unsigned)((t * TK + i * 8 + krow) * ld) + hv * KROW + kchunk : OOB;
+                const unsigned off = t < last ? (unsigned)((tile(t) * TK + i * 8 + krow) * ld) + hv * KROW + kchunk : OOB;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(to + hv * HALF + i * 1024), 16, off, 0, 0, 0);
             }
     };
@@ -703,23 +703,12 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
 
     issue(rk, ks, ldk, first);
     issue(rv, vs, ldv, first);
-    __builtin_amdgcn_sched_barrier(0);
-    {
-        // (in every wave, so that none has the queries still to wait for in the loop)
-        f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int h = 0; h < 2 * HV; ++h) s = mma(kf0[h], qf[h], s);
-        float mx = s[0];
-#pragma unroll
-        for (int v = 1; v < 4; ++v) mx = c >= 0.0f ? fmaxf(mx, s[v]) : fminf(mx, s[v]);
-        if (wave < 4) first_top[r * 16 + wave * 4 + g] = mx * c;
-    }
     auto start_top = [&]() __attribute__((always_inline)) {      // every wave comes here once
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wg_barrier();
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const f32x4 m = *(const f32x4 *)(first_top + r * 16 + 4 * w);
+        for (int w = 0; w < HV; ++w) {
+            const f32x4 m = *(const f32x4 *)(first_top + (w * 16 + r) * 4);
 #pragma unroll
             for (int v = 0; v < 4; ++v) top = fmaxf(top, m[v]);
         }
@@ -740,13 +729,12 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile has been read
         issue(rk, ks, ldk, t + 1);
-        if (t == first) start_top();                     // not before the first scores: the wait for the other waves is hidden behind theirs
-        if ((t + 1) * TK > Lk) {
+        if ((tile(t) + 1) * TK > Lk) {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (t * TK + kb * 16 + 4 * g + v >= Lk) s[kb][v] = c < 0.0f ? INFINITY : -INFINITY;
+                    if (tile(t) * TK + kb * 16 + 4 * g + v >= Lk) s[kb][v] = c < 0.0f ? INFINITY : -INFINITY;
         }
         float mx = s[0][0];
         if (c >= 0.0f) {
@@ -757,6 +745,10 @@ __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)
             for (int i = 1; i < 4 * KB; ++i) mx = fminf(mx, s[i >> 2][i & 3]);
         }
         float cand = mx * c;
+        if (t == first) {
+            if (tile(t) < HV) first_top[(tile(t) * 16 + r) * 4 + g] = cand;
+            start_top();
+        }
         if (__builtin_amdgcn_ballot_w64(cand > top + TAU) != 0) {
             cand = fmaxf(cand, __shfl_xor(cand, 16));
             cand = fmaxf(cand, __shfl_xor(cand, 32));
