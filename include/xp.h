@@ -26,10 +26,11 @@
  *   - Degenerate sizes: M, N or batch == 0 -> XP_OK, nothing launched.
  *     K == 0 -> C = beta * C (zero-filled when beta == 0).
  *   - beta == 0 means C is not read: NaN or Inf already in C never reach the result.
- *   - Matrices whose layout, alignment or size the tuned kernels do not cover (operands not
- *     contiguous along K, pointers or leading dimensions not multiples of 16 bytes, extents
- *     beyond 32-bit byte offsets within a tile) run on a slower general kernel instead of
- *     failing; the result obeys the same definition.
+ *   - Pointers, leading dimensions and extents that are no multiple of 16 bytes run on
+ *     matrix-core kernels of their own, slower than those for aligned operands.  What no tuned
+ *     kernel covers (operands contiguous along neither index, extents beyond 32-bit byte
+ *     offsets within a tile) runs on a general kernel instead of failing; the result obeys
+ *     the same definition.
  *   - Thread safety: entry points may be called concurrently; xp_force_config changes
  *     process-wide state and is meant for tuning sweeps and tests only.
  */
@@ -173,9 +174,9 @@ int xp_last_config(xp_op op, xp_dtype in_type);
  *                 var_i = (1/cols) sum_j (x(i,j) - mean_i)^2
  *   xp_rmsnorm    y(i,j) = x(i,j) / sqrt((1/cols) sum_j x(i,j)^2 + eps) * gamma(j)
  * gamma and beta are vectors of cols elements of x's type; NULL means all ones / all zeros.
- * eps must be finite and >= 0.  Rows whose length and alignment allow 16-byte accesses (cols a
- * multiple of 4 fp32 / 8 bf16 elements, 16-byte aligned rows) are read from memory exactly once;
- * other rows, and rows longer than 32768 fp32 / 65536 bf16 elements, take a general three-pass kernel.
+ * eps must be finite and >= 0.  Rows of 4 to 32768 fp32 / 8 to 65536 bf16 elements are read from
+ * memory exactly once, at any alignment (16-byte aligned ones of whole 16-byte chunks fastest);
+ * shorter and longer rows take a general three-pass kernel.
  */
 xp_status xp_softmax(int64_t rows, int64_t cols, const void *x, xp_dtype x_type, int64_t ldx,
                      void *y, xp_dtype y_type, int64_t ldy, void *stream);

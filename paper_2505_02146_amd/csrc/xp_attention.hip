@@ -631,8 +631,9 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(AttnParams p)
 // 43 us, where 16 compute units take 98 KB a microsecond each.
 // Every wave starts from the same reference maximum, that of the first 64 keys, which are the first tiles of one or two waves: the
 // waves meet once, after their first scores.  Probabilities are then rounded to bf16 against the reference that the other
-// kernels would hold, so that a query's result does not depend on how many queries are asked for with it (with references of
-// the waves' own it moved by 2e-3, two independent roundings).
+// kernels hold, so that a query has the same result among few and among many (with references of the waves' own it moved by
+// 2e-3, two independent roundings) -- unless a later score exceeds the reference by more than TAU: there every kernel moves it, for
+// all queries of a wave.
 // Layouts and steps are those of the kernels above, with tiles of 64 / HV keys.
 template <int HV, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_few_kernel(AttnParams p)

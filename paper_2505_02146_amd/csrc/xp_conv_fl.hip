@@ -10,8 +10,10 @@
 // data, which may be infinite).  The next tile's rows are requested before a tile is multiplied and go into the other LDS buffer
 // after it.  Blocks are computed transposed: a lane stores four consecutive channels of a pixel.
 //
-// Measured (32 images): the general kernel 334 us, the any-alignment kernel 57, this one 30.5 (3.7 TB/s); without its stores 20,
-// without its MFMAs 26.
+// Measured (32 images): the general kernel 335 us, the any-alignment kernel 57, this one 29 (3.9 TB/s); without its stores 20,
+// without its MFMAs 26.  No unit is the bound: of the time the matrix units are busy 13 %, the vector units 21 %, LDS 17 % (half of
+// it conflicts of the window reads); a workgroup's staging, products and stores follow one another, and 448 workgroups of
+// this call leave a fourth of the compute units with one instead of two.
 #include "xp_internal.hpp"
 #include "xp_any_align.hpp"
 #include "xp_lds_tr.hpp"
@@ -283,8 +285,9 @@ hipError_t fl_launch(const Problem &q)
 // first tile, costs more than the reuse saves (both sides timed over 1800 calls; pixels, time here over that of the any-alignment
 // kernel: 8000 1.2 .. 1.3, 50000 1.3, 80000 .. 100000 0.93 .. 1.04, 130000 0.64 .. 1.0; 247000 22 us and 39, the first layer's
 // 401408 29 and 56, 516128 17 and 40), above 128 output channels from 50000 on (75264 x 448 30 us and 43, 20000 1.3).  A filter
-// along its output channels is gathered element by element at the start and takes twice as many.  Four output rows or fewer leave waves of a tile without work, and long rows of few elements leave
-// few tiles: there it takes 250000 pixels and a tile for every compute unit (47 x 1 x 27594 x 6 -> 8, 5 taps 24 us and 48, but
+// along its output channels is gathered element by element at the start and takes twice as many.  Four output rows or fewer
+// leave waves of a tile without work, and long rows of few elements leave few tiles: there it takes 250000 pixels and a
+// tile for every compute unit (47 x 1 x 27594 x 6 -> 8, 5 taps 24 us and 48, but
 // 2 x 1 x 7427 x 1 -> 128, 15 taps, a tile per image, 56 and 6.3, 14 x 1 x 33664 x 1 -> 16, one tap, 67 and 36).  Where the any-alignment
 // kernel declines (fewer than 8 channels, filter along them) the other side is the general kernel: 0.2 .. 0.85 of its time
 // but for few rows and short filters.  The estimate is the output at a rate above any that others are priced at.

@@ -18,7 +18,7 @@
 // transposing reads (ds_read_b64_tr_b16 / _b8).  Blocks are computed transposed (16x16x32 bf16, 16x16x64 int8): a lane
 // stores four consecutive columns at once, at any 4-byte aligned address.
 //
-// Measured against the general kernel it takes over from: 2049 x 1021 x 1535 278 -> 27 us, 4001 x 4003 x 4005 180 us (710 TFLOP/s),
+// Measured against the general kernel it takes over from: 2049 x 1021 x 1535 278 -> 26 us, 4001 x 4003 x 4005 180 us (710 TFLOP/s),
 // int8 128 x 3196 x 4544 915 -> 19 us, 3x3 convolution 8 x 112 x 112 x 34 -> 44 205 -> 22 us.  Bound: a step's chain of LDS writes,
 // barrier and reads (64x64 .. 128x128 tiles, 0.33 .. 0.85 us a step where MFMAs take 0.06 .. 0.25).
 #include "xp_internal.hpp"
