@@ -258,7 +258,8 @@ const Variant kI8Fr = {"i8 few rows x 8 to 40 rows, eight waves split k, through
 // 76 and 107, 192 x 16 x 1024 x 1024 73 and 96).
 // 16 x 8192 x 8192 25 us here and 57, 16 x 4096 x 4096 7.8 and 18.7, 42 x 9266 x 11712 48 and 82; 192 problems 64 x 1024 x 64 97 and 15,
 // 96 problems 49 x 6144 x 48 297 and 27.  Rows off a 16-byte boundary (there: the any-alignment kernel) have the same lines
-// up to 128 tiles, and 0.78 .. 1.0 up to 16 rows and 256 tiles from 1 KB on.  A matrix-vector product with aligned rows (of
+// up to 128 tiles for at most 48 rows of X (more: 0.96 .. 1.6 beyond 32 tiles, 64 x 6976 x 3456 40 us here and 21), and 0.78 .. 1.0
+// up to 16 rows and 256 tiles from 1 KB on.  A matrix-vector product with aligned rows (of
 // any length) has a kernel of its own.
 bool few_rows_preferred(const Problem &q)
 {
@@ -270,6 +271,7 @@ bool few_rows_preferred(const Problem &q)
     const bool from_memory = n * kb * q.batch > 300000000;
     if (q.batch > 1 && !(from_memory && m <= 16) && tiles > (m <= 8 ? 256 : m <= 32 ? 128 : m <= 48 ? 64 : 16)) return false;
     if (tiles <= 32) return m <= 32 || kb >= 512;
+    if (m > 48 && !fr_aligned(q)) return false;
     if (tiles <= 64) return m <= 16 || kb >= (m <= 32 ? 256 : m <= 48 ? 1024 : 4096);
     if (tiles <= 128) return m <= 16 || kb >= (m <= 32 ? 1024 : m <= 48 ? 2048 : 4096);
     if (!fr_aligned(q)) return tiles <= 256 && m <= 16 && kb >= 1024;

@@ -39,6 +39,8 @@ def _gemm(xp, kind, batch, M, N, K, la="row", lb="col", skew=0):
     # many problems: a workgroup per 64-row tile of the other kernels is more than the chip holds at once
     ((96, 64, 687, 32), False), ((192, 64, 1024, 64), False), ((96, 49, 6144, 48), False), ((32, 33, 4096, 512), False),
     ((128, 17, 256, 2048), False), ((128, 1024, 7, 64), False), ((128, 64, 64, 4096), False), ((0, 64, 16384, 2048), False),
+    # rows off a 16-byte boundary: more than 48 rows against more than 32 tiles stay with the any-alignment kernel
+    ((0, 64, 6976, 6913), False), ((0, 49, 2112, 6913), False), ((0, 48, 6976, 6913), True), ((0, 64, 1728, 6913), True), ((0, 64, 6976, 6912), True),
 ])
 def test_few_rows(xp, kind, call, few):
     assert ("few rows" in _gemm(xp, kind, *call)) == few
