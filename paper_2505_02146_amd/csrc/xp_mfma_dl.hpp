@@ -665,7 +665,7 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
             if constexpr (EARLY) {
                 OutT *C = (OutT *)p.C + batch * p.strideC;
                 if (m0 + T::BM <= m_end && n0 + T::BN <= p.N && (INT8 || (p.beta == 0.0f && p.alpha == 1.0f)) &&
-                    (((unsigned long long)C | (unsigned long long)(p.ldc * (long long)sizeof(OutT))) & 15) == 0) {
+                    rows_aligned(C, p.ldc, 64)) {
                     early = C + (long long)(m0 + wm * T::WTM + (lane & 15)) * p.ldc + (n0 + wn * T::WTN + (lane >> 4) * 4);
                     early_step = 16 * p.ldc;
                 }
@@ -1011,11 +1011,11 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
     using OutT = typename std::conditional<INT8, int, float>::type;
     OutT *C = (OutT *)p.C + batch * p.strideC;
     if constexpr (MF == 16 && !PLANAR) {
-        // A tile that lies inside the matrix, beta == 0, 16-byte aligned rows: one address per lane for the whole wave
-        // tile (the block row adds a multiple of the pitch, the block column is an instruction constant), no test per
-        // block, and with alpha == 1 (or integers) the accumulators are stored as they are
+        // A tile that lies inside the matrix, beta == 0, rows on 64 bytes (the stores are written through, see rows_aligned):
+        // one address per lane for the whole wave tile (the block row adds a multiple of the pitch, the block column is
+        // an instruction constant), no test per block, and with alpha == 1 (or integers) the accumulators are stored as they are
         const bool whole = m0 + T::BM <= m_end && n0 + T::BN <= p.N && (INT8 || p.beta == 0.0f) &&
-                           (((unsigned long long)C | (unsigned long long)(p.ldc * (long long)sizeof(OutT))) & 15) == 0;
+                           rows_aligned(C, p.ldc, 64);
         if (whole) {
             typedef OutT out4 __attribute__((ext_vector_type(4)));
             OutT *base = C + (long long)(m0 + wm * T::WTM + (lane & 15)) * p.ldc + (n0 + wn * T::WTN + (lane >> 4) * 4);

@@ -210,8 +210,11 @@ hipError_t sk_launch(const Problem &q)
     p.strideA_b = q.strideA * esz; p.strideB_b = q.strideB * esz; p.strideC = q.strideC;
     p.alpha = q.alpha; p.beta = q.beta;
     p.tiles_n = (int)((q.N + BN - 1) / BN);
-    hipLaunchKernelGGL((sk_kernel<INT8, BN, STREAM>), dim3((unsigned)((q.M + BM - 1) / BM), (unsigned)q.batch), dim3(320), 0,
-                       q.stream, p);
+    const dim3 grid((unsigned)((q.M + BM - 1) / BM), (unsigned)q.batch);
+    // non-temporal stores need rows of C on 64 bytes (see rows_aligned): others go through the L2
+    const bool on64 = (((uintptr_t)q.C | (uintptr_t)(q.ldc * 4) | (uintptr_t)(q.strideC * 4)) & 63) == 0;
+    if (STREAM && on64) hipLaunchKernelGGL((sk_kernel<INT8, BN, true>), grid, dim3(320), 0, q.stream, p);
+    else hipLaunchKernelGGL((sk_kernel<INT8, BN, false>), grid, dim3(320), 0, q.stream, p);
     return hipGetLastError();
 }
 

@@ -1,0 +1,53 @@
+"""C with rows, bases and batch strides on every kind of boundary (4, 8, 16, 32 and 64 bytes): whole tiles, edges, both
+store forms, against the oracle.  Integer-valued operands: every kernel has to give the oracle's value exactly."""
+import numpy as np
+import pytest
+
+from paper_2505_02146_amd import inputs
+from tests.helpers import dev
+
+pytestmark = pytest.mark.gpu
+
+VARIANTS = ["256x256x128B waves 2x2 ring 3(A)+2(B) direct-to-lds, reads as assembly, sub-steps paired",
+            "256x256x128B waves 2x4 ring 3(A)+2(B) direct-to-lds, reads as assembly, mfma16",
+            "256x256x128B waves 2x4 ring 2 direct-to-lds mfma16",
+            "128x128x128B waves 2x2 ring 2(A)+2(B) direct-to-lds, reads as assembly, mfma16",
+            "64x128-stream x128B single-k-step producer/consumer nt-stores"]
+
+
+@pytest.mark.parametrize("kind", ["bf16", "i8"])
+@pytest.mark.parametrize("pad,base", [(0, 0), (1, 0), (2, 3), (4, 0), (8, 4), (16, 8), (16, 0)])
+def test_output_rows(oracle, kind, pad, base):
+    """256 + 16 rows and 256 + 8 columns of C: a whole tile and edges of two kinds; `pad` elements between rows, `base` in front."""
+    import torch
+    from paper_2505_02146_amd import xp
+    M, N, K, batch = 272, 264, 64, 2
+    ldc = N + pad + 8                                     # 272: rows on 64 bytes where pad and base are multiples of 16
+    if kind == "i8":
+        A, B = (inputs.int8_uniform((batch, s, K), 5, t) for s, t in ((M, 1), (N, 2)))
+    else:
+        A, B = (inputs.to_bf16_bits(inputs.small_integers((batch, s, K), 5, t)) for s, t in ((M, 1), (N, 2)))
+    ref = np.stack([oracle.gemm_i8(M, N, K, A[i], "row", B[i], "col") if kind == "i8" else oracle.gemm_float(M, N, K, A[i], "row", B[i], "col")
+                    for i in range(batch)])
+    a, b = dev(A), dev(B)
+    stride = M * ldc + pad
+    names = [xp.xp_describe_config(1, kind, v) for v in range(xp.xp_num_configs(1, kind))]
+    ran = 0
+    for text in VARIANTS:
+        for v in (i for i, n in enumerate(names) if text in n):
+            for alpha, beta in ((1.0, 0.0),) if kind == "i8" else ((1.0, 0.0), (2.0, 0.0), (1.0, 3.0)):
+                flat = torch.full((base + batch * stride,), 7, dtype=torch.int32 if kind == "i8" else torch.float32, device="cuda")
+                xp.xp_force_config(1, kind, v)
+                try:
+                    xp.xp_gemm_batched(batch, M, N, K, alpha, a, "row", K, M * K, b, "col", K, N * K, beta, flat[base:], "row", ldc, stride,
+                                       a_type=kind, b_type=kind)
+                finally:
+                    xp.xp_force_config(1, kind, -1)
+                got = flat.cpu().numpy()
+                assert np.all(got[:base] == 7)
+                for i in range(batch):
+                    c = got[base + i * stride:base + i * stride + M * ldc].reshape(M, ldc)
+                    assert np.array_equal(c[:, :N], alpha * ref[i] + beta * 7), (names[v], alpha, beta)
+                    assert np.all(c[:, N:] == 7), names[v]
+                ran += 1
+    assert ran >= len(VARIANTS)
