@@ -11,6 +11,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef unsigned int u32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 
 template <bool INT8> struct Kind;
 template <> struct Kind<false> {

@@ -41,9 +41,10 @@ void build_tables()
         n += rs_variants(types[s], g_table[s] + n);
         if (types[s] == XP_F32) n += f32_small_variants(g_table[s] + n);
         n += dl_pair_variants(types[s], g_table[s] + n);
-        n += ua_variants(types[s], g_table[s] + n);
+        if (types[s] != XP_F32) n += types[s] == XP_BF16 ? ua_variants_bf16(g_table[s] + n) : ua_variants_i8(g_table[s] + n);
         n += fr_variants(types[s], g_table[s] + n);
         n += fl_variants(types[s], g_table[s] + n);
+        if (types[s] != XP_F32) n += types[s] == XP_BF16 ? ua_gemm_variants_bf16(g_table[s] + n) : ua_gemm_variants_i8(g_table[s] + n);
         if (n > kMaxVariants) { fprintf(stderr, "xp: variant table overflow (%d)\n", n); abort(); }
         g_count[s] = n;
     }

@@ -77,7 +77,10 @@ int dl_asm_variants(xp_dtype in_type, const Variant **out);
 int dl_small_variants(xp_dtype in_type, const Variant **out);
 int rs_variants(xp_dtype in_type, const Variant **out);
 int dl_pair_variants(xp_dtype in_type, const Variant **out);
-int ua_variants(xp_dtype in_type, const Variant **out);
+int ua_variants_bf16(const Variant **out);
+int ua_variants_i8(const Variant **out);
+int ua_gemm_variants_bf16(const Variant **out);
+int ua_gemm_variants_i8(const Variant **out);
 int fr_variants(xp_dtype in_type, const Variant **out);
 bool few_rows_preferred(const Problem &q);                // the variant of fr_variants can run the call and is the better choice
 int fl_variants(xp_dtype in_type, const Variant **out);
@@ -125,22 +128,23 @@ inline double tile_cost_us(const Problem &q, int BM, int BN, int lds_bytes, int 
     return conc == 1 ? rounds * (t_work + t_lat) : rounds * (t_work > t_lat ? t_work : t_lat);
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  This renumbering gives XCD x (linear id
+// mod 8) a run of consecutive numbers, so that neighbouring tiles share an L2: a permutation of 0 .. total-1 for any
+// total (the first total % 8 XCDs take one more).
+__device__ __forceinline__ unsigned xcd_run(unsigned linear, unsigned total)
+{
+    const unsigned x = linear & 7u, more = total & 7u;
+    return x * (total >> 3) + (x < more ? x : more) + (linear >> 3);
+}
+
 // Batched launches with few tiles per problem: the workgroups of one problem have consecutive
 // linear ids and would be dealt round-robin to the 8 XCDs, so each XCD's L2 would fetch that
-// problem's operands again.  This renumbering gives XCD x (linear id mod 8) a contiguous run of
-// (tile, batch) pairs instead, so a problem's tiles share one L2.  Returns the renumbered
-// blockIdx.x in `x` and blockIdx.y in `y`; identity when the grid size is not a multiple of 8.
+// problem's operands again.  Returns the renumbered blockIdx.x in `x` and blockIdx.y in `y`.
 __device__ __forceinline__ void xcd_batch_remap(unsigned &x, unsigned &y)
 {
-    const unsigned gx = gridDim.x, total = gx * gridDim.y;
-    x = blockIdx.x;
-    y = blockIdx.y;
-    if ((total & 7) == 0) {
-        const unsigned lin = y * gx + x;
-        const unsigned ren = (lin & 7) * (total >> 3) + (lin >> 3);
-        x = ren % gx;
-        y = ren / gx;
-    }
+    const unsigned gx = gridDim.x, ren = xcd_run(blockIdx.y * gx + blockIdx.x, gx * gridDim.y);
+    x = gridDim.y == 1 ? ren : ren % gx;
+    y = gridDim.y == 1 ? 0u : ren / gx;
 }
 
 // One-dimensional launches whose neighbouring workgroups share cache lines (window overlap, the heads
