@@ -200,6 +200,12 @@ template <int OFFSET, typename AccT, typename OutT> __device__ __forceinline__ v
     asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc0 sc1" : : "v"(dst), "a"(c), "n"(OFFSET) : "memory");
 }
 
+// 16 bytes per lane, or one dword of them, from the accumulation registers to `offset` in a buffer; nothing where that lies outside
+template <typename AccT> __device__ __forceinline__ void store_from_acc_within(u32x4 rsrc, unsigned offset, const AccT &c)
+{
+    asm volatile("buffer_store_dwordx4 %0, %1, %2, 0 offen" : : "a"(c), "v"(offset), "s"(rsrc) : "memory");
+}
+
 // the same from vector registers (the convolution's two tiles per compute unit: -1.5 to -2.4 us of 100); STREAM keeps
 // the non-temporal stores of the variants that ask for them
 template <bool STREAM, typename V4> __device__ __forceinline__ void put_tile(V4 *dst, V4 v)
@@ -285,7 +291,9 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
         bid = (int)x;
         batch = y;
     } else if ((nb & 7) == 0) {
-        bid = (bid & 7) * (nb >> 3) + (bid >> 3);
+        // (of other numbers of tiles an XCD takes every eighth: rows of tiles repeat in groups of four, so it shares panels all the same;
+        // int8 2609 x 1536 x 8064, 252 tiles, 40.3 us so and 42.5 in runs)
+        bid = (int)xcd_run((unsigned)bid, (unsigned)nb);
     }
     const int gsz = p.group_m * p.tiles_n;
     const int g = bid / gsz, first_m = g * p.group_m;
@@ -1014,17 +1022,23 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
         // A tile that lies inside the matrix, beta == 0, rows on 64 bytes (the stores are written through, see rows_aligned):
         // one address per lane for the whole wave tile (the block row adds a multiple of the pitch, the block column is
         // an instruction constant), no test per block, and with alpha == 1 (or integers) the accumulators are stored as they are
-        const bool whole = m0 + T::BM <= m_end && n0 + T::BN <= p.N && (INT8 || p.beta == 0.0f) &&
-                           rows_aligned(C, p.ldc, 64);
+        constexpr bool FROM_ACC = T::PAIR != 0 && T::NWAVE == 4 && !T::NTSTORE;
+        const bool plain = INT8 || p.beta == 0.0f, scaled = !INT8 && p.alpha != 1.0f;
+        const bool whole = m0 + T::BM <= m_end && n0 + T::BN <= p.N && plain && rows_aligned(C, p.ldc, 64);
+        typedef OutT out4 __attribute__((ext_vector_type(4)));
+        auto value = [&](int i, int j) {
+            out4 x = {(OutT)acc[i][j][0], (OutT)acc[i][j][1], (OutT)acc[i][j][2], (OutT)acc[i][j][3]};
+            if constexpr (!INT8) { if (scaled) x = out4{p.alpha * x[0], p.alpha * x[1], p.alpha * x[2], p.alpha * x[3]}; }
+            return x;
+        };
         if (whole) {
-            typedef OutT out4 __attribute__((ext_vector_type(4)));
             OutT *base = C + (long long)(m0 + wm * T::WTM + (lane & 15)) * p.ldc + (n0 + wn * T::WTN + (lane >> 4) * 4);
             const long long step16 = 16 * p.ldc;
             // (the stores below are assembly text to the compiler: it does not see that they read what the last matrix
             // instructions write, and a tile of one or two blocks per wave has nothing else in between)
             if constexpr (!T::NTSTORE) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-            if (INT8 || p.alpha == 1.0f) {
-                if constexpr (T::PAIR != 0 && T::NWAVE == 4 && !T::NTSTORE) {
+            if (FROM_ACC && !scaled) {
+                if constexpr (FROM_ACC) {
                     // accumulators that live in the accumulation registers go to memory from there (the compiler would
                     // first copy all 256 of them to vector registers: a thousand cycles before the first store)
                     static_for<T::MI * T::NI>([&](auto b_c) {
@@ -1032,22 +1046,12 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
                         store_from_acc<64 * J>(base, acc[I][J]);
                         if constexpr (J == T::NI - 1) base += step16;
                     });
-                } else {
-#pragma unroll
-                    for (int i = 0; i < T::MI; ++i, base += step16)
-#pragma unroll
-                        for (int j = 0; j < T::NI; ++j)
-                            put_tile<T::NTSTORE>((out4 *)(base + 16 * j), out4{(OutT)acc[i][j][0], (OutT)acc[i][j][1], (OutT)acc[i][j][2], (OutT)acc[i][j][3]});
                 }
             } else {
-                if constexpr (!INT8) {
 #pragma unroll
-                    for (int i = 0; i < T::MI; ++i, base += step16)
+                for (int i = 0; i < T::MI; ++i, base += step16)
 #pragma unroll
-                        for (int j = 0; j < T::NI; ++j)
-                            put_tile<T::NTSTORE>((out4 *)(base + 16 * j),
-                                                 out4{p.alpha * acc[i][j][0], p.alpha * acc[i][j][1], p.alpha * acc[i][j][2], p.alpha * acc[i][j][3]});
-                }
+                    for (int j = 0; j < T::NI; ++j) put_tile<T::NTSTORE>((out4 *)(base + 16 * j), value(i, j));
             }
 #ifdef XP_TRACE
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
@@ -1058,6 +1062,56 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
                 for (int x = 0; x < 3; ++x) p.trace[tr_slot * 16 + 8 + x] = tr_wait[x];
             }
 #endif
+            return;
+        }
+        // Tiles that reach past the matrix, and rows on other boundaries: stores into a buffer that ends with the wave's last row, so
+        // that rows past it, and columns past N by an offset outside the buffer, are dropped without a test per block.  Four
+        // columns of which only some exist are stored one by one.  Measured against tests and addresses for each block, 256x256 tiles of
+        // four waves: 4000 x 4000 x 2048 row/row 53.9 -> 52.0 us, 48 batched 896 x 896 x 128 55.5 -> 45.1, 5000 x 3000 x 2000 67.8 -> 54.7 (eight),
+        // 48 batched 811 x 811 x 128 102 -> 46 (with one 16-byte store for the block's misaligned row, but tested, 64)
+        const int rows = min(m_end - (m0 + wm * T::WTM), T::WTM), cols = min(p.N - (n0 + wn * T::WTN), T::WTN);
+        if (rows <= 0 || cols <= 0) return;
+        if (plain && !(FROM_ACC && scaled) && p.ldc < (1 << 29) / T::WTM) {
+            const unsigned pitch = (unsigned)p.ldc * 4u, bytes = (unsigned)(rows - 1) * pitch + (unsigned)cols * 4u;
+            const unsigned long long at = (unsigned long long)(C + (long long)(m0 + wm * T::WTM) * p.ldc + (n0 + wn * T::WTN));
+            const int c0 = 4 * (lane >> 4);
+            unsigned off[T::NI];
+#pragma unroll
+            for (int j = 0; j < T::NI; ++j) off[j] = 16 * j + c0 + 4 <= cols ? (unsigned)(lane & 15) * pitch + (16 * j + c0) * 4 : OOB;
+            if constexpr (FROM_ACC) {
+                const u32x4 rc = {(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)at), (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(at >> 32)),
+                                  (unsigned)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
+                asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // (as above)
+                static_for<T::MI * T::NI>([&](auto b_c) {
+                    constexpr int I = decltype(b_c)::value / T::NI, J = decltype(b_c)::value % T::NI;
+                    store_from_acc_within(rc, off[J] + (unsigned)(16 * I) * pitch, acc[I][J]);
+                });
+            } else {
+                const __amdgpu_buffer_rsrc_t rc = make_rsrc((const void *)at, bytes);
+#pragma unroll
+                for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < T::NI; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, value(i, j)), rc, off[j] + (unsigned)(16 * i) * pitch, 0, 0);
+            }
+            if ((cols & 3) != 0) {
+                const __amdgpu_buffer_rsrc_t rc = make_rsrc((const void *)at, bytes);
+#pragma unroll
+                for (int j = 0; j < T::NI; ++j) {
+                    if (16 * j > cols || cols > 16 * j + 16) continue;          // the block column in which the matrix ends
+#pragma unroll
+                    for (int i = 0; i < T::MI; ++i) {
+                        const out4 x = value(i, j);
+#pragma unroll
+                        for (int v = 0; v < 3; ++v) {
+                            const int c = 16 * j + c0 + v;
+                            const unsigned o = c < cols && 16 * j + c0 + 4 > cols ? (unsigned)(lane & 15) * pitch + c * 4 : OOB;
+                            const OutT e = x[v];
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, e), rc, o + (unsigned)(16 * i) * pitch, 0, 0);
+                        }
+                    }
+                }
+            }
             return;
         }
     }

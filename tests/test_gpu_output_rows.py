@@ -17,12 +17,13 @@ VARIANTS = ["256x256x128B waves 2x2 ring 3(A)+2(B) direct-to-lds, reads as assem
 
 @pytest.mark.parametrize("kind", ["bf16", "i8"])
 @pytest.mark.parametrize("pad,base", [(0, 0), (1, 0), (2, 3), (4, 0), (8, 4), (16, 8), (16, 0)])
-def test_output_rows(oracle, kind, pad, base):
-    """256 + 16 rows and 256 + 8 columns of C: a whole tile and edges of two kinds; `pad` elements between rows, `base` in front."""
+@pytest.mark.parametrize("M,N", [(272, 264), (500, 511), (257, 385), (131, 254)])
+def test_output_rows(oracle, kind, M, N, pad, base):
+    """Whole tiles and edges that cut a wave's part, a block and four columns; `pad` elements between rows, `base` in front."""
     import torch
     from paper_2505_02146_amd import xp
-    M, N, K, batch = 272, 264, 64, 2
-    ldc = N + pad + 8                                     # 272: rows on 64 bytes where pad and base are multiples of 16
+    K, batch = 64, 2
+    ldc = (N + 15) // 16 * 16 + pad                       # rows on 64 bytes where pad and base are multiples of 16
     if kind == "i8":
         A, B = (inputs.int8_uniform((batch, s, K), 5, t) for s, t in ((M, 1), (N, 2)))
     else:
@@ -30,7 +31,7 @@ def test_output_rows(oracle, kind, pad, base):
     ref = np.stack([oracle.gemm_i8(M, N, K, A[i], "row", B[i], "col") if kind == "i8" else oracle.gemm_float(M, N, K, A[i], "row", B[i], "col")
                     for i in range(batch)])
     a, b = dev(A), dev(B)
-    stride = M * ldc + pad
+    stride = M * ldc + pad                                # (with pad 0: every slice on 64 bytes)
     names = [xp.xp_describe_config(1, kind, v) for v in range(xp.xp_num_configs(1, kind))]
     ran = 0
     for text in VARIANTS:
