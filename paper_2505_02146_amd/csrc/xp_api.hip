@@ -129,7 +129,7 @@ struct TunedIndex {
     }
 };
 
-int tuned_variant(const Problem &q)
+int tuned_variant(const Problem &q, bool *exact)
 {
     static const TunedIndex index;
     const bool a_kc = q.conv || q.a_sk == 1, b_kc = q.b_sk == 1;
@@ -139,7 +139,7 @@ int tuned_variant(const Problem &q)
         if (t.op == q.op && t.type == q.in_type && t.batch == q.batch && t.M == q.M && t.N == q.N && t.K == q.K && t.a_kc == a_kc &&
             t.b_kc == b_kc) {
             const int v = index.variant[i];
-            if (v >= 0 && variant(q.in_type, v)->can_run(q)) return v;
+            if (v >= 0 && variant(q.in_type, v)->can_run(q)) { *exact = true; return v; }
             // (an entry whose variant declines this call -- a planar output, say -- leaves it to a later entry for the shape)
         }
     }
@@ -159,6 +159,77 @@ int tuned_variant(const Problem &q)
     return best;
 }
 
+// Fitted times (400 random calls, this rule on and off: 37 more than 5 % faster, 3 slower, which the two limits below now leave
+// out; bf16 128 x 512 x 4352 col/row 40.8 -> 15.7 us, 38 batched 640 x 640 x 128 23.2 -> 15.0, convolution 4 x 112 x 112 x 320 -> 53, 5x5 110 -> 78,
+// 104 batched 192 x 192 x 64 7.0 -> 5.0).  The neighbour rule and the variants' own estimates miss by 10 % in the geometric mean over random calls (the best of
+// all variants against the one chosen); a small model fitted to each variant's timings misses by 3 to 4:
+//   start + rounds x (per tile + steps x per step),   at least start + output x us a MB
+// rounds: 1 up to a tile per compute unit; beyond, `whole` of them count as whole rounds, and tile and step have times of their
+// own.  Rows of C off 64 bytes lengthen a tile.  The neighbour's choice stands unless the model sees 8 % more in another: the fit
+// is good to some per cent, the table's entries were timed.
+struct FittedTime {
+    const char *name;
+    bool candidate;                                       // the rest serve the comparison only: another was never slower
+    int bm, bn, step;
+    float start, tile, tile_shared, per_step, per_step_shared, whole, misaligned, per_mb;
+};
+#include "xp_fitted_times.inc"
+constexpr double kFittedGain = 1.08;
+
+struct FittedTable {
+    const FittedTime *rows;
+    int count;
+    int variant[64];
+    FittedTable(const FittedTime *r, int n, xp_dtype type) : rows(r), count(n)
+    {
+        const int all = num_variants(type);
+        for (int i = 0; i < n; ++i) {
+            variant[i] = -1;
+            for (int v = 0; v < all; ++v)
+                if (strcmp(xp::variant(type, v)->name, r[i].name) == 0) variant[i] = v;
+        }
+    }
+};
+
+double fitted_us(const FittedTime &f, const Problem &q)
+{
+    const double x = (double)((q.M + f.bm - 1) / f.bm) * (f.bn ? (double)((q.N + f.bn - 1) / f.bn) : 1.0) * (double)q.batch / 256.0;
+    const double steps = f.bn ? __builtin_ceil((double)q.K * elem_size(q.in_type) / f.step) : __builtin_ceil((double)q.N / f.step);
+    const double rounds = x <= 1.0 ? 1.0 : f.whole * __builtin_ceil(x) + (1.0 - f.whole) * x;
+    const double tile = (x <= 1.0 ? f.tile : f.tile_shared) * (q.ldc % 16 != 0 ? 1.0 + f.misaligned : 1.0);
+    const double work = rounds * (tile + (x <= 1.0 ? f.per_step : f.per_step_shared) * steps);
+    const double store = (double)q.M * (double)q.N * (double)q.batch * 4e-6 * f.per_mb;
+    return f.start + (work > store ? work : store);
+}
+
+// `chosen`, or a variant that is faster by the model.  Calls like those it was fitted to: aligned operands, row-major output, at most
+// 140 GFLOP and 400 MB of output, 150 of one matrix (6784 x 7227 x 704, 196 MB: 110 us by the neighbour, 134 by the model); a matrix
+// times a vector has a kernel of its own.
+int faster_by_fit(const Problem &q, int chosen)
+{
+    if (q.in_type == XP_F32 || q.c_plane || q.N == 1 || q.K <= 0 || any_alignment_needed(q)) return chosen;
+    const double out = (double)q.M * (double)q.N * (double)q.batch;
+    if (2.0 * out * (double)q.K > 1.4e11 || out * 4.0 > (q.batch > 1 ? 4e8 : 1.5e8)) return chosen;
+    static_assert(sizeof kFitBf16 / sizeof *kFitBf16 <= 64 && sizeof kFitI8 / sizeof *kFitI8 <= 64 && sizeof kFitConv / sizeof *kFitConv <= 64, "FittedTable::variant");
+    static const FittedTable bf16(kFitBf16, sizeof kFitBf16 / sizeof *kFitBf16, XP_BF16), i8(kFitI8, sizeof kFitI8 / sizeof *kFitI8, XP_I8),
+        conv(kFitConv, sizeof kFitConv / sizeof *kFitConv, XP_BF16);
+    const FittedTable &t = q.conv ? conv : (q.in_type == XP_I8 ? i8 : bf16);
+    int best = -1;
+    double best_us = 1e30, chosen_us = 1e30;
+    for (int i = 0; i < t.count; ++i) {
+        const int v = t.variant[i];
+        if (v < 0 || !variant(q.in_type, v)->can_run(q)) continue;
+        const double us = fitted_us(t.rows[i], q);
+        if (v == chosen) chosen_us = us;
+        // (walking over all columns of 64 rows takes a workgroup for every compute unit: 8 batched 752 x 752 x 64, 96 of them, 7.1 us and 8.4)
+        if (!t.rows[i].bn && (q.M + t.rows[i].bm - 1) / t.rows[i].bm * q.batch < 256) continue;
+        // (tiles whose waves share out a step's K, of the kernel for any alignment: long sums, where they are 1.3 to 2.8 times as fast)
+        if (t.rows[i].bn && t.rows[i].step > 128 && q.K * elem_size(q.in_type) < 4096) continue;
+        if (t.rows[i].candidate && us < best_us) { best_us = us; best = v; }
+    }
+    return best >= 0 && chosen_us > kFittedGain * best_us ? best : chosen;
+}
+
 int select_uncached(const Problem &q)
 {
     const int learned = runtime_tuned_variant(q);        // shapes tuned in this process or loaded from a file
@@ -171,8 +242,9 @@ int select_uncached(const Problem &q)
         for (int i = 1; i < n; ++i)
             if (variant(q.in_type, i) == few) return i;
     }
-    const int tuned = tuned_variant(q);
-    if (tuned >= 0) return tuned;
+    bool exact = false;
+    const int tuned = tuned_variant(q, &exact);
+    if (tuned >= 0) return exact ? tuned : faster_by_fit(q, tuned);
     int best = 0;
     double best_cost = variant(q.in_type, 0)->cost(q);
     for (int i = 1; i < n; ++i) {
@@ -181,7 +253,7 @@ int select_uncached(const Problem &q)
         const double c = v->cost(q);
         if (c < best_cost) { best_cost = c; best = i; }
     }
-    return best;
+    return faster_by_fit(q, best);
 }
 
 // Programs call the same few shapes over and over, and a table walk costs microseconds that a small
@@ -207,7 +279,7 @@ int select_variant(const Problem &q)
     static thread_local SelSlot cache[SLOTS];
     SelKey k;
     k.op = q.op; k.type = q.in_type; k.kc = ((q.conv || q.a_sk == 1) ? 1 : 0) | (q.b_sk == 1 ? 2 : 0);
-    k.batch = q.batch; k.M = q.M; k.N = q.N; k.K = q.K; k.planar = q.c_plane != 0;
+    k.batch = q.batch; k.M = q.M; k.N = q.N; k.K = q.K; k.planar = (q.c_plane != 0 ? 1 : 0) | (q.ldc % 16 != 0 ? 2 : 0);        // (the fitted times read whether rows of C lie on 64 bytes)
     k.misaligned = misaligned_bits(q);
     const int64_t geom[9] = {q.H, q.W, q.Cin, q.R, q.S, q.sh, q.sw, q.ph, q.pw};
     for (int i = 0; i < 9; ++i) k.geom[i] = q.conv ? geom[i] : 0;

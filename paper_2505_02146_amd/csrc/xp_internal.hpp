@@ -77,6 +77,7 @@ int dl_asm_variants(xp_dtype in_type, const Variant **out);
 int dl_small_variants(xp_dtype in_type, const Variant **out);
 int rs_variants(xp_dtype in_type, const Variant **out);
 int dl_pair_variants(xp_dtype in_type, const Variant **out);
+bool any_alignment_needed(const Problem &q);              // operands that only the kernels for any alignment take
 int ua_variants_bf16(const Variant **out);
 int ua_variants_i8(const Variant **out);
 int ua_gemm_variants_bf16(const Variant **out);

@@ -29,6 +29,8 @@ XP_UA_GEMM_VARIANT(kUa64x32, 64, 32, 2, 1, 4, false, false, "", 1.39, 2.92, 2.66
 
 }  // namespace
 
+bool any_alignment_needed(const Problem &q) { return ua_needed(q); }
+
 int ua_variants_bf16(const Variant **out)
 {
     out[0] = &kUa128; out[1] = &kUa128x64; out[2] = &kUa64;
