@@ -144,8 +144,8 @@ __device__ __forceinline__ unsigned xcd_run(unsigned linear, unsigned total)
 __device__ __forceinline__ void xcd_batch_remap(unsigned &x, unsigned &y)
 {
     const unsigned gx = gridDim.x, ren = xcd_run(blockIdx.y * gx + blockIdx.x, gx * gridDim.y);
-    x = gridDim.y == 1 ? ren : ren % gx;
-    y = gridDim.y == 1 ? 0u : ren / gx;
+    x = ren % gx;
+    y = ren / gx;
 }
 
 // One-dimensional launches whose neighbouring workgroups share cache lines (window overlap, the heads
