@@ -4,8 +4,8 @@
 //
 // The direct-to-LDS kernels need 16-byte rows; here the tiles pass through registers, and a chunk may start at any
 // element (a 16-byte load at an odd multiple of 2 bytes costs 10 to 20 % of the kernel: 2048 x 1024 x 1534 17.0 us, x 1535
-// 17.3 to 18.5; cutting chunks out of dword-aligned loads instead was slower, 30 us against 27 at 2049 x 1021 x 1535, whether
-// the fifth dword was loaded or taken from the next lane).  Care is needed where a chunk is not wholly inside its operand:
+// 17.3 to 18.5; cutting chunks of 128 bytes a row out of dword-aligned loads was slower, 30 us against 27 at 2049 x 1021 x 1535, whether
+// the fifth dword was loaded or taken from the next lane: it pays with 256 bytes a row, below).  Care is needed where a chunk is not wholly inside its operand:
 //   GEMM   rows (columns) past the edge are clamped to the last one, their results are not stored; a chunk along K past the
 //          end exists in the last K step only, which takes a checked path (zeros past K).  A chunk along M or N may run
 //          into the next k row, which is memory of the operand in every step but the last.
