@@ -204,7 +204,9 @@ double fitted_us(const FittedTime &f, const Problem &q)
 
 // `chosen`, or a variant that is faster by the model.  Calls like those it was fitted to: aligned operands, row-major output, at most
 // 140 GFLOP and 400 MB of output, 150 of one matrix (6784 x 7227 x 704, 196 MB: 110 us by the neighbour, 134 by the model); a matrix
-// times a vector has a kernel of its own.
+// times a vector has a kernel of its own.  A choice that the model knows nothing of stands, as there is nothing to compare: bf16
+// 4096 x 4096 x 4032 col/col keeps the 256x256 tiles of the entry beside it, 93 us, and not the best of the model's variants, 169; int8
+// 96 batched 512 x 512 x 64 and x 128 the walk over columns, 17.9 and 18.7 us, and not 64x64 tiles, 19.4 and 22.3.
 int faster_by_fit(const Problem &q, int chosen)
 {
     if (q.in_type == XP_F32 || q.c_plane || q.N == 1 || q.K <= 0 || any_alignment_needed(q)) return chosen;
@@ -215,7 +217,7 @@ int faster_by_fit(const Problem &q, int chosen)
         conv(kFitConv, sizeof kFitConv / sizeof *kFitConv, XP_BF16);
     const FittedTable &t = q.conv ? conv : (q.in_type == XP_I8 ? i8 : bf16);
     int best = -1;
-    double best_us = 1e30, chosen_us = 1e30;
+    double best_us = 1e30, chosen_us = -1.0;               // (no row: nothing to compare with)
     for (int i = 0; i < t.count; ++i) {
         const int v = t.variant[i];
         if (v < 0 || !variant(q.in_type, v)->can_run(q)) continue;

@@ -5,6 +5,29 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+def _run(kind, batch, M, N, K, la, lb):
+    """The name of the variant that was chosen; its result has to be the general kernel's."""
+    import torch
+    from paper_2505_02146_amd import xp
+    op, n = (1, batch) if batch else (0, 1)
+    a, b = (torch.randint(-4, 5, (n * r * K,), device="cuda").to(torch.bfloat16 if kind == "bf16" else torch.int8) for r in (M, N))
+    lda, ldb = K if la == "row" else M, N if lb == "row" else K
+    out = []
+    for v in (-1, 0):                                            # integers: the general kernel's sums are exact too
+        c = torch.full((n * M * N,), 7, device="cuda", dtype=torch.float32 if kind == "bf16" else torch.int32)
+        xp.xp_force_config(op, kind, v)
+        try:
+            xp.xp_gemm_batched(n, M, N, K, 1.0, a, la, lda, M * K, b, lb, ldb, N * K, 0.0, c, "row", N, M * N) if batch else \
+                xp.xp_gemm(M, N, K, 1.0, a, la, lda, b, lb, ldb, 0.0, c, "row", N)
+            if v < 0:
+                name = xp.xp_describe_config(op, kind, xp.xp_last_config(op, kind))
+        finally:
+            xp.xp_force_config(op, kind, -1)
+        out.append(c)
+    assert torch.equal(*out)
+    return name
+
+
 @pytest.mark.parametrize("batch,M,N,K,la,lb,text", [
     (0, 128, 512, 4352, "col", "row", "unaligned rows"),         # a long sum and few tiles: K shared out over a workgroup's waves
     (0, 384, 1152, 5696, "col", "row", "unaligned rows"),
@@ -14,23 +37,20 @@ pytestmark = pytest.mark.gpu
     (8, 752, 752, 64, "row", "col", "128B"),                     # too few rows of tiles to walk over columns
 ])
 def test_fitted_choice(batch, M, N, K, la, lb, text):
-    import torch
-    from paper_2505_02146_amd import xp
-    op, n = (1, batch) if batch else (0, 1)
-    a, b = (torch.randint(-4, 5, (n * r * K,), device="cuda").bfloat16() for r in (M, N))
-    lda, ldb = K if la == "row" else M, N if lb == "row" else K
-    out = []
-    for v in (-1, 0):                                            # integers: the general kernel's sums are exact too
-        c = torch.full((n * M * N,), 7.0, device="cuda")
-        xp.xp_force_config(op, "bf16", v)
-        try:
-            xp.xp_gemm_batched(n, M, N, K, 1.0, a, la, lda, M * K, b, lb, ldb, N * K, 0.0, c, "row", N, M * N) if batch else \
-                xp.xp_gemm(M, N, K, 1.0, a, la, lda, b, lb, ldb, 0.0, c, "row", N)
-            if v < 0:
-                name = xp.xp_describe_config(op, "bf16", xp.xp_last_config(op, "bf16"))
-        finally:
-            xp.xp_force_config(op, "bf16", -1)
-        out.append(c)
-    assert torch.equal(*out)
+    name = _run("bf16", batch, M, N, K, la, lb)
     assert text in name, name
     assert ("stream" in text) == ("stream" in name), name
+
+
+@pytest.mark.parametrize("kind,batch,M,N,K,la,lb,text", [
+    ("bf16", 0, 4096, 4096, 4032, "col", "col", "256x256"), ("bf16", 0, 4096, 4096, 1088, "col", "col", "256x256"),
+    ("bf16", 0, 2048, 8192, 1088, "col", "col", "256x256"), ("bf16", 0, 4096, 4096, 4032, "col", "row", "256x256"),
+    ("bf16", 0, 3072, 3072, 3008, "col", "row", "256x256"), ("bf16", 0, 1632, 6624, 592, "col", "col", "256x256"),
+    ("bf16", 0, 1536, 8192, 4160, "row", "col", "224x256"),
+    ("i8", 96, 512, 512, 64, "row", "col", "64x64-stream"), ("i8", 96, 512, 512, 128, "row", "col", "64x64-stream"),
+    ("i8", 32, 1024, 1024, 128, "row", "col", "64x64-stream"),
+])
+def test_a_choice_without_a_fitted_time_stands(kind, batch, M, N, K, la, lb, text):
+    """Neighbours of swept shapes whose winners were timed faster than every variant with a fitted time."""
+    name = _run(kind, batch, M, N, K, la, lb)
+    assert text in name, name
