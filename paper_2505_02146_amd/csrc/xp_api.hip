@@ -159,17 +159,21 @@ int tuned_variant(const Problem &q, bool *exact)
     return best;
 }
 
-// Fitted times (400 random calls, this rule on and off: 37 more than 5 % faster, 3 slower, which the two limits below now leave
-// out; bf16 128 x 512 x 4352 col/row 40.8 -> 15.7 us, 38 batched 640 x 640 x 128 23.2 -> 15.0, convolution 4 x 112 x 112 x 320 -> 53, 5x5 110 -> 78,
-// 104 batched 192 x 192 x 64 7.0 -> 5.0).  The neighbour rule and the variants' own estimates miss by 10 % in the geometric mean over random calls (the best of
-// all variants against the one chosen); a small model fitted to each variant's timings misses by 3 to 4:
+// Fitted times.  Over random aligned calls the neighbour rule and the variants' own estimates take 13 % longer than the best of all variants
+// in the geometric mean, this rule 9 (4000 calls that neither the fit nor the choice of candidates had seen: 667 choices displaced, 472 of them
+// more than 5 % faster, 55 more than 5 % slower, 1.28 at worst; bf16 128 x 512 x 4352 col/row 31.6 -> 14.2 us, 38 batched 640 x 640 x 128 23.3 ->
+// 15.3, convolution 4 x 112 x 112 x 320 -> 53, 5x5 111 -> 80).  A small model, fitted to timings of each variant:
 //   start + rounds x (per tile + steps x per step),   at least start + output x us a MB
 // rounds: 1 up to a tile per compute unit; beyond, `whole` of them count as whole rounds, and tile and step have times of their
 // own.  Rows of C off 64 bytes lengthen a tile.  The neighbour's choice stands unless the model sees 8 % more in another: the fit
 // is good to some per cent, the table's entries were timed.
 struct FittedTime {
     const char *name;
-    bool candidate;                                       // the rest serve the comparison only: another was never slower
+    // the rest serve the comparison only: in the calls of the fit, all layouts together, another variant was never slower, or the
+    // timings of 13900 random calls refute the row: with the 128x128 k-group tiles, the 64x64 ring of three and the 256x128 64-byte tiles of
+    // the convolution as candidates, 2754 choices were displaced, 1882 for a faster variant and 336 for a slower one (by more than 5 %); without, 2610,
+    // 1883 and 218.  With every other row as a candidate, 2921, 2027 and 284
+    bool candidate;
     int bm, bn, step;
     float start, tile, tile_shared, per_step, per_step_shared, whole, misaligned, per_mb;
 };

@@ -54,3 +54,38 @@ def test_a_choice_without_a_fitted_time_stands(kind, batch, M, N, K, la, lb, tex
     """Neighbours of swept shapes whose winners were timed faster than every variant with a fitted time."""
     name = _run(kind, batch, M, N, K, la, lb)
     assert text in name, name
+
+
+@pytest.mark.parametrize("kind,batch,M,N,K,la,lb,text", [
+    # rows that the timings refuted are no candidates: the choice stands ...
+    ("bf16", 0, 2304, 5800, 504, "col", "row", "256x256x128B"), ("bf16", 0, 1768, 640, 64, "row", "row", "128x64x128B"),
+    ("i8", 0, 6784, 272, 224, "col", "col", "64x64x128B"), ("i8", 7, 528, 528, 64, "row", "row", "64x64x128B"),
+    # ... and others displace it
+    ("i8", 0, 256, 256, 8192, "col", "row", "unaligned rows"), ("i8", 0, 208, 416, 6144, "row", "row", "unaligned rows"),
+])
+def test_candidates(kind, batch, M, N, K, la, lb, text):
+    name = _run(kind, batch, M, N, K, la, lb)
+    assert text in name, name
+
+
+@pytest.mark.parametrize("n,h,cin,cout,r,stride,pad,text", [
+    (53, 14, 32, 272, 1, 1, 0, "128x128x64B"), (3, 112, 32, 328, 1, 2, 0, "128x128x64B"), (27, 112, 320, 192, 1, 2, 0, "224x256x128B"),
+    (4, 112, 320, 53, 5, 1, 2, "256x128x128B waves 4x2"),
+])
+def test_candidates_of_convolutions(n, h, cin, cout, r, stride, pad, text):
+    import torch
+    from paper_2505_02146_amd import xp
+    x, f = (torch.randint(-2, 3, (e,), device="cuda").bfloat16() for e in (n * h * h * cin, cout * r * r * cin))
+    P, out = (h + 2 * pad - r) // stride + 1, []
+    for v in (-1, 0):
+        c = torch.full((n * P * P * cout,), 7.0, device="cuda")
+        xp.xp_force_config(2, "bf16", v)
+        try:
+            xp.xp_conv2d_nhwc(n, h, h, cin, cout, r, r, stride, stride, pad, pad, x, f, "krsc", c)
+            if v < 0:
+                name = xp.xp_describe_config(2, "bf16", xp.xp_last_config(2, "bf16"))
+        finally:
+            xp.xp_force_config(2, "bf16", -1)
+        out.append(c)
+    assert torch.equal(*out)
+    assert text in name, name
