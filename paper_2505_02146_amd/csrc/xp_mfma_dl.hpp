@@ -276,6 +276,17 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
     long long tr_wait[3] = {0, 0, 0};                   // paired loop, wave 0: cycles waiting for global loads, in the barrier, and from entry to the first load
     const int tr_slot = (int)(blockIdx.y * gridDim.x + blockIdx.x) + (m_base ? (int)(gridDim.x * gridDim.y) : 0);
     tr_c[0] = clock64(); tr_w[0] = wall_clock64();
+    auto trace_end = [&] {                              // at every exit: the stores have reached L2
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+        tr_c[3] = clock64(); tr_w[3] = wall_clock64();
+        if (p.trace && tid == 0) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) { p.trace[tr_slot * 16 + x] = tr_c[x]; p.trace[tr_slot * 16 + 4 + x] = tr_w[x]; }
+            for (int x = 0; x < 3; ++x) p.trace[tr_slot * 16 + 8 + x] = tr_wait[x];
+        }
+    };
+#else
+    auto trace_end = [] {};
 #endif
 
     // workgroup -> tile: one XCD (workgroup id mod 8) owns a run of consecutive tiles, walked in
@@ -841,14 +852,8 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
                     static_for<T::NI>([&](auto j_c) { store_from_acc<64 * decltype(j_c)::value>(early, acc[T::MI - 1][decltype(j_c)::value]); });
 #ifdef XP_TRACE
                     tr_c[2] = clock64(); tr_w[2] = wall_clock64();
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-                    tr_c[3] = clock64(); tr_w[3] = wall_clock64();
-                    if (p.trace && tid == 0) {
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) { p.trace[tr_slot * 16 + x] = tr_c[x]; p.trace[tr_slot * 16 + 4 + x] = tr_w[x]; }
-                        for (int x = 0; x < 3; ++x) p.trace[tr_slot * 16 + 8 + x] = tr_wait[x];
-                    }
 #endif
+                    trace_end();
                     return;
                 }
             }
@@ -1053,15 +1058,7 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
 #pragma unroll
                     for (int j = 0; j < T::NI; ++j) put_tile<T::NTSTORE>((out4 *)(base + 16 * j), value(i, j));
             }
-#ifdef XP_TRACE
-            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-            tr_c[3] = clock64(); tr_w[3] = wall_clock64();
-            if (p.trace && tid == 0) {
-#pragma unroll
-                for (int x = 0; x < 4; ++x) { p.trace[tr_slot * 16 + x] = tr_c[x]; p.trace[tr_slot * 16 + 4 + x] = tr_w[x]; }
-                for (int x = 0; x < 3; ++x) p.trace[tr_slot * 16 + 8 + x] = tr_wait[x];
-            }
-#endif
+            trace_end();
             return;
         }
         // Tiles that reach past the matrix, and rows on other boundaries: stores into a buffer that ends with the wave's last row, so
@@ -1070,7 +1067,10 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
         // four waves: 4000 x 4000 x 2048 row/row 53.9 -> 52.0 us, 48 batched 896 x 896 x 128 55.5 -> 45.1, 5000 x 3000 x 2000 67.8 -> 54.7 (eight),
         // 48 batched 811 x 811 x 128 102 -> 46 (with one 16-byte store for the block's misaligned row, but tested, 64)
         const int rows = min(m_end - (m0 + wm * T::WTM), T::WTM), cols = min(p.N - (n0 + wn * T::WTN), T::WTN);
-        if (rows <= 0 || cols <= 0) return;
+        if (rows <= 0 || cols <= 0) {
+            trace_end();
+            return;
+        }
         if (plain && !(FROM_ACC && scaled) && p.ldc < (1 << 29) / T::WTM) {
             const unsigned pitch = (unsigned)p.ldc * 4u, bytes = (unsigned)(rows - 1) * pitch + (unsigned)cols * 4u;
             const unsigned long long at = (unsigned long long)(C + (long long)(m0 + wm * T::WTM) * p.ldc + (n0 + wn * T::WTN));
@@ -1112,6 +1112,7 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
                     }
                 }
             }
+            trace_end();
             return;
         }
     }
@@ -1129,15 +1130,7 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
                 store_block16t<INT8, T::NTSTORE>(acc[i][j], C, p.ldc, m0 + wm * T::WTM + i * 16, n0 + wn * T::WTN + j * 16, lane, m_end,
                                      p.N, p.alpha, p.beta);
         }
-#ifdef XP_TRACE
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));         // the stores have reached L2
-    tr_c[3] = clock64(); tr_w[3] = wall_clock64();
-    if (p.trace && tid == 0) {
-#pragma unroll
-        for (int x = 0; x < 4; ++x) { p.trace[tr_slot * 16 + x] = tr_c[x]; p.trace[tr_slot * 16 + 4 + x] = tr_w[x]; }
-        for (int x = 0; x < 3; ++x) p.trace[tr_slot * 16 + 8 + x] = tr_wait[x];
-    }
-#endif
+    trace_end();
 }
 
 template <bool INT8, class T, int MODE>

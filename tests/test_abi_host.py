@@ -296,6 +296,19 @@ def test_entry_points_resolve_their_builders():
     assert 'import_module("oracle.build")' in inspect.getsource(entry.build)
 
 
+def test_every_exit_of_the_direct_to_lds_kernels_writes_its_time_stamps():
+    """The diagnostic build's record (-DXP_TRACE): each way out of dl_body behind the K loop goes through trace_end."""
+    text = (ROOT / "paper_2505_02146_amd" / "csrc" / "xp_mfma_dl.hpp").read_text()
+    body = text[text.index("void dl_body("):]
+    body = body[:body.index("\n}\n")]
+    lines = [l.split("//")[0].strip() for l in body[body.index("    // epilogue"):].splitlines()]
+    lines = [l for l in lines if l and not l.startswith("#")]
+    exits = [i for i, l in enumerate(lines) if re.search(r"\breturn;", l)]
+    assert len(exits) >= 3
+    for i in exits + [len(lines)]:
+        assert lines[i - 1] == "trace_end();", lines[i - 1:i + 1]
+
+
 def test_status_strings(lib):
     from paper_2505_02146_amd import xp
     seen = {xp.status_string(i) for i in range(9)}
