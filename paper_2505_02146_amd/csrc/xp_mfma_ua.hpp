@@ -12,7 +12,8 @@
 //   conv   for a filter row r the taps (s, c) of a pixel are one run of S*Cin consecutive elements of the image, and of the
 //          filter: K is walked as R runs, each padded to whole chunks.  What of a chunk lies outside the image (left or
 //          right) or past the run is an interval of its elements: it is loaded with the rest and masked with zeros.
-// A chunk that would leave the whole operand is loaded from its last (first) 16 bytes and shifted into place.
+// A chunk that would leave the whole operand is loaded from its last (first) 16 bytes and shifted into place.  Loads from dwords
+// take a dword whole: up to three bytes that share it with the first element of an operand, and lie before that, come along unused.
 // Structure: two LDS buffers; one or two steps' loads fly while a step is multiplied; one barrier a step.  Operands along K lie in
 // LDS as rows of a step's bytes, operands along M or N as they lie in memory and come back through the transposing reads
 // (ds_read_b64_tr_b16 / _b8).  Blocks are computed transposed (16x16x32 bf16, 16x16x64 int8): a lane stores four consecutive
@@ -645,13 +646,13 @@ hipError_t ua_launch(const Problem &q)
     p.a_ext = q.conv ? (q.M / (q.P * q.Q)) * q.H * q.W * q.Cin * esz
                      : ((af == A_OC ? (q.K - 1) * q.a_sk + q.M : (q.M - 1) * q.a_sm + q.K)) * esz;
     p.b_ext = (b_oc ? (q.K - 1) * q.b_sk + q.N : (q.N - 1) * q.b_sn + q.K) * esz;
-    // rows that start inside a dword (GEMM): loads from dwords, put in place between the lanes
-    const bool sh = T::SHIFT && !q.conv &&
+    // rows that start inside a dword (GEMM): loads from dwords, put in place between the lanes.  Rows of a dword or less are loaded
+    // as they lie: the dword in which the operand's last row starts would end behind it
+    const bool sh = T::SHIFT && !q.conv && q.K * esz > 4 &&
                     (((uintptr_t)q.A | (uintptr_t)q.B | (uintptr_t)p.lda_b | (uintptr_t)p.ldb_b | (uintptr_t)(q.strideA * esz) | (uintptr_t)(q.strideB * esz)) & 3) != 0;
     // unchecked steps: all of K inside (and, of loads from dwords, the dword behind it), and for an operand along M or N a k
     // row after the step's last one
     p.full = (int)((q.K - (af == A_OC || b_oc ? 1 : 0) - (sh ? 4 / esz : 0)) / (T::STEPB / esz));
-    if (q.K < 4 / esz + 1) p.full = 0;
     p.ldc = q.ldc; p.c_plane = q.c_plane;
     p.strideA_b = q.strideA * esz; p.strideB_b = q.strideB * esz; p.strideC = q.strideC;
     p.alpha = q.alpha; p.beta = q.beta;

@@ -10,9 +10,10 @@ pytestmark = pytest.mark.gpu
 
 NAN_BITS = 0x7FC0
 LAYOUTS = [("row", "col"), ("row", "row"), ("col", "row"), ("col", "col")]
-# a step is 64 to 256 bf16 (128 to 512 int8) of K: K below one, whole steps with one element more or less, several unchecked steps and
-# a rest; extents around 32, 64, 96, 128 and 192, one of them a single row
-SHAPES = [(1, 17, 5), (33, 31, 64), (97, 65, 257), (129, 95, 511), (193, 129, 1535), (64, 191, 2051), (96, 97, 2816)]
+# a step is 64 to 256 bf16 (128 to 512 int8) of K: K of 1 to 5 (rows around a dword), below one step, whole steps with one element
+# more or less, several unchecked steps and a rest; extents around 32, 64, 96, 128 and 192, a single row and a single column
+SHAPES = [(1, 17, 5), (33, 31, 1), (98, 33, 2), (97, 65, 3), (100, 97, 4), (129, 95, 5), (1, 40, 67), (50, 1, 259),
+          (33, 31, 64), (97, 65, 257), (129, 95, 511), (193, 129, 1535), (64, 191, 2051), (96, 97, 2816)]
 
 
 @pytest.fixture(scope="module")
@@ -30,10 +31,18 @@ def _forced(xp, op, kind):
     return found
 
 
+def _taken(outer, K, along_k, ld, epc):
+    """An operand of a chunk or more (epc elements); stored along its outer index, with a pitch of a chunk or more."""
+    if along_k or ld == 1:
+        return (outer - 1) * (ld if along_k else 1) + K >= epc
+    return ld >= epc and (K - 1) * ld + outer >= epc
+
+
 @pytest.mark.parametrize("kind", ["bf16", "i8"])
 @pytest.mark.parametrize("la,lb", LAYOUTS)
 def test_unaligned_rows(xp, oracle, kind, la, lb):
     import torch
+    ran = 0
     for n, (M, N, K) in enumerate(SHAPES):
         for skew in (0, 1, 3):                           # elements in front of the operands: rows inside and on dwords
             make = (lambda s, t: inputs.int8_uniform(s, n, t)) if kind == "i8" else (lambda s, t: inputs.to_bf16_bits(inputs.normal(s, n, t)))
@@ -47,18 +56,23 @@ def test_unaligned_rows(xp, oracle, kind, la, lb):
             for v in _forced(xp, 0, kind):
                 xp.xp_force_config(0, kind, v)
                 c = torch.full((M, N), 7, dtype=torch.int32 if kind == "i8" else torch.float32, device="cuda")
+                what = f"{kind} {M}x{N}x{K} {la}/{lb} skew {skew} {xp.xp_describe_config(0, kind, v)}"
+                epc = 16 if kind == "i8" else 8
+                taken = _taken(M, K, la == "row", lda, epc) and _taken(N, K, lb == "col", ldb, epc)
                 try:
                     xp.xp_gemm(M, N, K, 1.0, da[skew:], la, lda, db[skew:], lb, ldb, 0.0, c, "row", N, a_type=kind, b_type=kind)
-                except xp.XpError as e:                  # an operand or a pitch along M or N below one chunk is declined
-                    assert e.status == 6 and (min(M, N) * K < 16 or (la == "col" and lda < 16) or (lb == "row" and ldb < 16))
+                except xp.XpError as e:
+                    assert e.status == 6 and not taken, what
                     continue
                 finally:
                     xp.xp_force_config(0, kind, -1)
-                what = f"{kind} {M}x{N}x{K} {la}/{lb} skew {skew} {xp.xp_describe_config(0, kind, v)}"
+                assert taken, what
+                ran += 1
                 if kind == "i8":
                     assert np.array_equal(c.cpu().numpy(), ref), what
                 else:
                     check_float(c.cpu().numpy(), ref, what)
+    assert ran >= 3 * 6 * 11                             # of 14 shapes, three skews, six variants
 
 
 @pytest.mark.parametrize("la,lb", LAYOUTS)
