@@ -693,9 +693,11 @@ bool ua_needed(const Problem &q)
 // Estimated time: start + rounds x (per tile + K steps x per step).  Up to one tile per compute unit is one round, beyond it `whole` of
 // them count as whole rounds, and tile and step have times of their own (a unit's workgroups hide each other's waits); an operand along M or
 // N adds its share to a step.  Fitted for each tile to timings of 780 (int8: 450) products of 64 to 8192 a side, odd and even, of all
-// layouts; the choice it makes takes 2 % longer than the best of the nine in the geometric mean (the three tiles and the
-// estimate before it: 9 %).  Where the operands are aligned the direct-to-LDS kernels are up to twice as fast (2048 x 1024 x 1536: 11
-// us, this kernel 14), whatever their estimates say.
+// layouts; the share of A along M, for int8 and the dealt-out tile, to 6000 more, as that fit had left it at the ends of its range (-0.2,
+// 0.5: int8 1280 x 256 x 6584 col/col 36.5 -> 16.3 us).  Over 11800 random calls the choice takes 2.9 % longer than the best of the nine in the
+// geometric mean, the three tiles and the estimate before it 7.7; of the choices that differ 56 % are more than 5 % faster, 10 % slower.
+// Where the operands are aligned the direct-to-LDS kernels are up to twice as fast (2048 x 1024 x 1536: 11 us, this kernel 14),
+// whatever their estimates say.
 struct UaTimes { double start, tile, tile_shared, step, step_shared, a_outer, b_outer, whole; };
 template <class T>
 double ua_cost(const Problem &q, const UaTimes &u)

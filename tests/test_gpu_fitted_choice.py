@@ -68,6 +68,19 @@ def test_candidates(kind, batch, M, N, K, la, lb, text):
     assert text in name, name
 
 
+@pytest.mark.parametrize("kind,batch,M,N,K,la,lb,text", [
+    # tiles for rows on any element, A along M: what that adds to a step
+    ("i8", 0, 1280, 256, 6584, "col", "col", "64x32 waves"), ("i8", 0, 140, 148, 5132, "col", "col", "64x32 waves"),
+    ("i8", 0, 7731, 1896, 3102, "col", "col", "128x128x128B waves 2x2 any"), ("i8", 0, 1132, 4680, 6776, "col", "row", "192x128"),
+    ("i8", 61, 134, 134, 128, "col", "row", "64x64x128B waves 2x2 any"), ("bf16", 26, 410, 129, 414, "col", "col", "64x64x128B waves 2x2 any"),
+    ("bf16", 159, 769, 128, 769, "col", "col", "128x128x128B waves 2x2 any"),
+    ("bf16", 0, 2049, 1021, 1535, "row", "row", "96x96"),
+])
+def test_choice_of_tiles_for_any_alignment(kind, batch, M, N, K, la, lb, text):
+    name = _run(kind, batch, M, N, K, la, lb)
+    assert text in name, name
+
+
 @pytest.mark.parametrize("n,h,cin,cout,r,stride,pad,text", [
     (53, 14, 32, 272, 1, 1, 0, "128x128x64B"), (3, 112, 32, 328, 1, 2, 0, "128x128x64B"), (27, 112, 320, 192, 1, 2, 0, "224x256x128B"),
     (4, 112, 320, 53, 5, 1, 2, "256x128x128B waves 4x2"),
