@@ -13,7 +13,7 @@ namespace xp {
 
 namespace {
 
-constexpr int kMaxVariants = 128;                       // 68 bf16 variants at the last count; checked in build_tables
+constexpr int kMaxVariants = 128;                       // 79 bf16 variants at the last count; checked in build_tables
 const Variant *g_table[3][kMaxVariants];
 int g_count[3] = {0, 0, 0};
 std::once_flag g_once;
@@ -159,14 +159,15 @@ int tuned_variant(const Problem &q, bool *exact)
     return best;
 }
 
-// Fitted times.  Over random aligned calls the neighbour rule and the variants' own estimates take 13 % longer than the best of all variants
-// in the geometric mean, this rule 9 (4000 calls that neither the fit nor the choice of candidates had seen: 667 choices displaced, 472 of them
-// more than 5 % faster, 55 more than 5 % slower, 1.28 at worst; bf16 128 x 512 x 4352 col/row 31.6 -> 14.2 us, 38 batched 640 x 640 x 128 23.3 ->
-// 15.3, convolution 4 x 112 x 112 x 320 -> 53, 5x5 111 -> 80).  A small model, fitted to timings of each variant:
+// Fitted times.  Over random aligned calls the neighbour rule and the variants' own estimates take 9.5 % longer than the best of all variants
+// in the geometric mean, this rule 6.0 (time_variants.py, 10000 calls of seed 21, with this rule and without it: 1666 choices displaced, 1162 of them
+// more than 5 % faster, 151 more than 5 % slower, 1.49 at worst; bf16 128 x 512 x 4352 col/row 31.6 -> 14.2 us, 38 batched 640 x 640 x 128 23.3 ->
+// 15.3, convolution 4 x 112 x 112 x 320 -> 53, 5x5 111 -> 80).  By family, displaced / faster / slower: bf16 673 / 459 / 50, int8 327 / 278 / 20, batched bf16
+// 380 / 199 / 63, batched int8 34 / 16 / 6, convolutions 252 / 210 / 12.  A small model, fitted to timings of each variant:
 //   start + rounds x (per tile + steps x per step),   at least start + output x us a MB
 // rounds: 1 up to a tile per compute unit; beyond, `whole` of them count as whole rounds, and tile and step have times of their
 // own.  Rows of C off 64 bytes lengthen a tile.  The neighbour's choice stands unless the model sees 8 % more in another: the fit
-// is good to some per cent, the table's entries were timed.
+// is good to some per cent, the table's entries were timed (a line of 5 %: 1283 faster and 182 slower, of 15 %: 924 and 93).
 struct FittedTime {
     const char *name;
     // the rest serve the comparison only: in the calls of the fit, all layouts together, another variant was never slower, or the
@@ -207,7 +208,7 @@ double fitted_us(const FittedTime &f, const Problem &q)
 }
 
 // `chosen`, or a variant that is faster by the model.  Calls like those it was fitted to: aligned operands, row-major output, at most
-// 140 GFLOP and 400 MB of output, 150 of one matrix (6784 x 7227 x 704, 196 MB: 110 us by the neighbour, 134 by the model); a matrix
+// 140 GFLOP and 400 MB of output (no line of the card's: the fit saw none beyond them), 150 MB of one matrix (6784 x 7227 x 704, 196 MB: 110 us by the neighbour, 134 by the model); a matrix
 // times a vector has a kernel of its own.  A choice that the model knows nothing of stands, as there is nothing to compare: bf16
 // 4096 x 4096 x 4032 col/col keeps the 256x256 tiles of the entry beside it, 93 us, and not the best of the model's variants, 169; int8
 // 96 batched 512 x 512 x 64 and x 128 the walk over columns, 17.9 and 18.7 us, and not 64x64 tiles, 19.4 and 22.3.
