@@ -200,7 +200,7 @@ template <int OFFSET, typename AccT, typename OutT> __device__ __forceinline__ v
     asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc0 sc1" : : "v"(dst), "a"(c), "n"(OFFSET) : "memory");
 }
 
-// 16 bytes per lane, or one dword of them, from the accumulation registers to `offset` in a buffer; nothing where that lies outside
+// 16 bytes per lane from the accumulation registers to `offset` in a buffer; nothing where that lies outside
 template <typename AccT> __device__ __forceinline__ void store_from_acc_within(u32x4 rsrc, unsigned offset, const AccT &c)
 {
     asm volatile("buffer_store_dwordx4 %0, %1, %2, 0 offen" : : "a"(c), "v"(offset), "s"(rsrc) : "memory");

@@ -101,7 +101,7 @@ struct Operand {
     static constexpr int BYTES = CH * RSTEP * ROWB;
     static constexpr unsigned ALL = (1u << EPC) - 1;
     static_assert(NT % CPR == 0 && (RSTEP % 16 == 0 || CH == 1), "whole rounds of the workgroup; the swizzle is a thread's");
-    static_assert(!SH || OC || CPR == 16, "a row's chunks in the sixteen lanes that exchange their last dwords");
+    static_assert(!SH || (OC ? CPR <= 16 : CPR == 16), "a row's chunks in the sixteen lanes that exchange their dwords");
 
     // chunk swizzle of an LDS row (bank-conflict-free fragment reads; constant over a thread's rows)
     static __device__ __forceinline__ int swz(int row)
@@ -213,7 +213,7 @@ struct Operand {
                               __builtin_amdgcn_alignbyte(x[2], x[1], sh[i]), __builtin_amdgcn_alignbyte(x[3], x[2], sh[i])};
                 } else {
                     // the loads begin in the dword of the chunk's first element: its last elements are in the lane to the right's first dword
-                    const unsigned behind = __builtin_amdgcn_update_dpp(0u, x[0], CPR > 16 ? 0x130 : 0x101, 0xf, 0xf, false);   // wave_shl:1, row_shl:1
+                    const unsigned behind = __builtin_amdgcn_update_dpp(0u, x[0], 0x101, 0xf, 0xf, false);   // row_shl:1
                     x = u32x4{__builtin_amdgcn_alignbyte(x[1], x[0], sh[i]), __builtin_amdgcn_alignbyte(x[2], x[1], sh[i]),
                               __builtin_amdgcn_alignbyte(x[3], x[2], sh[i]), __builtin_amdgcn_alignbyte(behind, x[3], sh[i])};
                 }
@@ -305,12 +305,12 @@ enum { A_K = 0, A_OC = 1, A_CONV = 2 };
 
 // The workgroup: WM x WN waves over the tile, KG groups of them over a step's K (each takes SUBB bytes of it; their sums meet
 // in LDS at the end).  PF: register sets of loads.  WPS: waves per SIMD that the registers have to allow.  DEALT, SHIFT: loads dealt out,
-// from dwords (see the head of the file).
+// from dwords (see the head of the file).  BASIC: four waves and one K group; these take convolutions too, and the shortest sums of products.
 template <int BM_, int BN_, int WM_, int WN_, int KG_, int PF_, int WPS_ = 2, bool DEALT_ = false, bool SHIFT_ = false>
 struct UaTile {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KG = KG_, PF = PF_, WPS = WPS_;
     static constexpr int NT = 64 * WM * WN * KG, STEPB = SUBB * KG;
-    static constexpr bool DEALT = DEALT_, SHIFT = SHIFT_, CONV = KG_ == 1 && !DEALT_ && WM_ * WN_ == 4;
+    static constexpr bool DEALT = DEALT_, SHIFT = SHIFT_, BASIC = KG_ == 1 && !DEALT_ && WM_ * WN_ == 4;
 };
 
 template <bool INT8, int AF, bool B_OC, bool SH, class T>
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(T::NT, T::WPS) void ua_kernel(UaParams p)
         if constexpr (AF == A_CONV) {
             a.template load_checked<SET>(step, p);
             b.template load_checked<SET>(step, p);
-        } else if constexpr (T::CONV) {
+        } else if constexpr (T::BASIC) {
             // (these tiles serve the shortest sums, where the time to fetch the kernel's code counts: one path)
             a.template load_checked<SET>(step, p);
             b.template load_checked<SET>(step, p);
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(T::NT, T::WPS) void ua_kernel(UaParams p)
     typedef std::integral_constant<bool, false> False;
     static_for<PF>([&](auto u) {
         if (u < p.steps) {
-            if (T::CONV && AF != A_CONV && u < p.full) load(u, u, std::integral_constant<int, 0>{}, std::integral_constant<int, LOADS>{});
+            if (T::BASIC && AF != A_CONV && u < p.full) load(u, u, std::integral_constant<int, 0>{}, std::integral_constant<int, LOADS>{});
             else load_any(u, u);
         }
     });
@@ -666,7 +666,7 @@ hipError_t ua_launch(const Problem &q)
 #define XP_UA(AF, BO, SH) hipLaunchKernelGGL((ua_kernel<INT8, AF, BO, SH, T>), grid, dim3(T::NT), 0, q.stream, p)
 #define XP_UA_GEMM(SH) do { if (af == A_K) { if (b_oc) XP_UA(A_K, true, SH); else XP_UA(A_K, false, SH); } else { if (b_oc) XP_UA(A_OC, true, SH); else XP_UA(A_OC, false, SH); } } while (0)
     if (q.conv) {
-        if constexpr (!INT8 && T::CONV) { if (b_oc) XP_UA(A_CONV, true, false); else XP_UA(A_CONV, false, false); }
+        if constexpr (!INT8 && T::BASIC) { if (b_oc) XP_UA(A_CONV, true, false); else XP_UA(A_CONV, false, false); }
     } else if constexpr (T::SHIFT) {
         if (sh) XP_UA_GEMM(true); else XP_UA_GEMM(false);
     } else XP_UA_GEMM(false);
@@ -695,7 +695,8 @@ bool ua_needed(const Problem &q)
 // N adds its share to a step.  Fitted for each tile to timings of 780 (int8: 450) products of 64 to 8192 a side, odd and even, of all
 // layouts; the share of A along M, for int8 and the dealt-out tile, to 6000 more, as that fit had left it at the ends of its range (-0.2,
 // 0.5: int8 1280 x 256 x 6584 col/col 36.5 -> 16.3 us).  Over 11800 random calls the choice takes 2.9 % longer than the best of the nine in the
-// geometric mean, the three tiles and the estimate before it 7.7; of the choices that differ 56 % are more than 5 % faster, 10 % slower.
+// geometric mean, the three tiles and the estimate before it 7.7; of the choices that differ 56 % are more than 5 % faster, 10 % slower.  Over 3549
+others (time_variants.py --align any, seed 31, those that need these tiles) 2.4 % longer, 1.51 at worst.
 // Where the operands are aligned the direct-to-LDS kernels are up to twice as fast (2048 x 1024 x 1536: 11 us, this kernel 14),
 // whatever their estimates say.
 struct UaTimes { double start, tile, tile_shared, step, step_shared, a_outer, b_outer, whole; };
@@ -716,7 +717,7 @@ double ua_cost(const Problem &q, const UaTimes &u)
     const double sides = 1.0 + (q.a_sk != 1 ? u.a_outer : 0.0) + (q.b_sk != 1 ? u.b_outer : 0.0);
     const double us = u.start + rounds * (x <= 1.0 ? u.tile + u.step * sides * steps : u.tile_shared + u.step_shared * sides * steps);
     // (a tie goes to the tiles of one K group and four waves: the fit is good to some per cent)
-    return us * (ua_needed(q) ? 1.0 : 8.0) * (T::CONV ? 1.0 : 1.02);
+    return us * (ua_needed(q) ? 1.0 : 8.0) * (T::BASIC ? 1.0 : 1.02);
 }
 
 }  // namespace
