@@ -696,7 +696,7 @@ bool ua_needed(const Problem &q)
 // layouts; the share of A along M, for int8 and the dealt-out tile, to 6000 more, as that fit had left it at the ends of its range (-0.2,
 // 0.5: int8 1280 x 256 x 6584 col/col 36.5 -> 16.3 us).  Over 11800 random calls the choice takes 2.9 % longer than the best of the nine in the
 // geometric mean, the three tiles and the estimate before it 7.7; of the choices that differ 56 % are more than 5 % faster, 10 % slower.  Over 3549
-others (time_variants.py --align any, seed 31, those that need these tiles) 2.4 % longer, 1.51 at worst.
+// others (time_variants.py --align any, seed 31, those that need these tiles) 2.4 % longer, 1.51 at worst.
 // Where the operands are aligned the direct-to-LDS kernels are up to twice as fast (2048 x 1024 x 1536: 11 us, this kernel 14),
 // whatever their estimates say.
 struct UaTimes { double start, tile, tile_shared, step, step_shared, a_outer, b_outer, whole; };
