@@ -1065,13 +1065,15 @@ __device__ __forceinline__ void dl_body(const DlParams &p, char *lds, int bid, i
         // that rows past it, and columns past N by an offset outside the buffer, are dropped without a test per block.  Four
         // columns of which only some exist are stored one by one.  Measured against tests and addresses for each block, 256x256 tiles of
         // four waves: 4000 x 4000 x 2048 row/row 53.9 -> 52.0 us, 48 batched 896 x 896 x 128 55.5 -> 45.1, 5000 x 3000 x 2000 67.8 -> 54.7 (eight),
-        // 48 batched 811 x 811 x 128 102 -> 46 (with one 16-byte store for the block's misaligned row, but tested, 64)
+        // 48 batched 811 x 811 x 128 102 -> 46 (with one 16-byte store for the block's misaligned row, but tested, 64).  Not for the bf16 tile
+        // of four waves whose sub-steps are not paired: its 256 accumulators spill 236 registers then, 20 without
+        constexpr bool BOUNDED = INT8 || T::PAIR != 0 || T::MI * T::NI < 64;
         const int rows = min(m_end - (m0 + wm * T::WTM), T::WTM), cols = min(p.N - (n0 + wn * T::WTN), T::WTN);
         if (rows <= 0 || cols <= 0) {
             trace_end();
             return;
         }
-        if (plain && !(FROM_ACC && scaled) && p.ldc < (1 << 29) / T::WTM) {
+        if (BOUNDED && plain && !(FROM_ACC && scaled) && p.ldc < (1 << 29) / T::WTM) {
             const unsigned pitch = (unsigned)p.ldc * 4u, bytes = (unsigned)(rows - 1) * pitch + (unsigned)cols * 4u;
             const unsigned long long at = (unsigned long long)(C + (long long)(m0 + wm * T::WTM) * p.ldc + (n0 + wn * T::WTN));
             const int c0 = 4 * (lane >> 4);
