@@ -19,9 +19,10 @@
 // (ds_read_b64_tr_b16 / _b8).  Blocks are computed transposed (16x16x32 bf16, 16x16x64 int8): a lane stores four consecutive
 // columns at once, at any 4-byte aligned address.
 //
-// What bounds it, found by leaving parts out (2049 x 1021 x 1535, 96x96 tiles on 242 of 256 compute units, 12 steps of 128 k): the loads
-// alone take 16 us of 19, LDS writes 1, fragment reads and MFMAs 2; a unit takes 65 KB/us of rows that start on any
-// element, 98 of rows on 16 bytes.  So tiles are chosen to fill the card once, and:
+// What bounds it, by time stamps (2049 x 1021 x 1535, 18.6 us, 96x96 tiles on 242 of 256 compute units, 12 steps of 128 k): 3.1 us to the first
+// step in LDS, 8 steps in the loop at 0.73 us (67 KB/us of loads), the last four, on the path for any step, at 1.25, 0.8 for the groups'
+// sums, 1.2 for the stores, 2.7 outside the workgroups.  By themselves a unit's loads run at 65 KB/us of rows that start on any element, 98 of rows
+// on 16 bytes.  So tiles are chosen to fill the card once, and:
 //   K groups   tiles of 32x64, 64x32 and 64x64 by eight waves, a quarter or half of a step's K each (their sums meet in LDS): few
 //              tiles and a long K.  75 x 3719 x 6108 31.9 -> 19.7 us, 896 x 104 x 5196 26.8 -> 17.3, int8 216 x 923 x 6985 26 -> 17
 //   eight waves over 192x128: half the bytes a flop of 64x64, for large products.  2624 x 4450 x 5376 157 -> 139
